@@ -281,7 +281,10 @@ int fm_set_graph_launch(int enable);
  * later solves and batches.  A pass whose launch would hold fewer than
  * about four blocks per compute unit is timed with its tiles repeated up to
  * that fill (time divided by the repetitions): its cost when other solves
- * share the device, as in fm_batch_solve and the server.
+ * share the device, as in fm_batch_solve and the server.  A plan whose
+ * spectral part runs on the matrix-core transforms (short and odd axes)
+ * keeps them when they are faster than the five chosen passes together;
+ * choice and ms describe the axis passes in either case.
  * choice[5] (host, optional) receives the chosen candidate per pass;
  * ms[4*5] (host, optional) the mean time in ms per candidate and pass (-1 if
  * not applicable).  Overwrites the plan's displacement and spectral buffers

@@ -143,6 +143,19 @@ struct SolveDev {
   const double* c0_sc[3];  // per axis: sin(xi/2)[U], then cos(xi/2)[U]
 };
 
+// One axis of one component as the matrix-core transforms see it (fm_mat.h).
+enum MatClass : int { MC_FOLD = 0, MC_SPLIT = 1, MC_CPLX = 2 };
+struct MatAxis {
+  int32_t kind, n, cls;
+  int32_t kt;                     // 16-row tiles of the half matrices
+  int32_t rlf, rli;               // matrix steps of the last tile, forward and inverse
+  int32_t cU, cV;                 // slots of the two halves
+  int32_t j0, j1;                 // nodes that carry data: [j0, j1)
+  const void *fU, *fV, *iU, *iV;  // half matrices in fragment order
+  const double* gs;               // per half and slot: sin^2, cos^2 of the half frequency
+  const void* gz;                 // the same in the plan's precision
+};
+
 // One axis pass of one component of one solve (device).
 struct PassDesc {
   int32_t solve;
@@ -167,6 +180,9 @@ struct PassDesc {
   const double* gc2[3];           // cos^2(xi/2)
   int32_t scheme, green_lam;      // green_lam: 1 uses lambda0 (B0), 0 for 2mu0
   double h, lam0, mu0;
+  MatAxis mx[3];                  // matrix-core passes: the component's axes
+  int32_t pair;                   // 1: some axis transforms complex data (its plane kernel pairs real and imaginary parts)
+  const Ctrl* ctrl;               // control block of the solve
 };
 
 }  // namespace fm

@@ -28,6 +28,7 @@
 #include "fm_wave.h"
 #include "fm_green_c0.h"
 #include "fm_finite.h"
+#include "fm_mat.h"
 
 using namespace fm;
 
@@ -49,6 +50,7 @@ int fail(int code, const std::string& msg) {
 constexpr size_t ALIGN = 256;
 inline size_t align_up(size_t v, size_t a = ALIGN) { return (v + a - 1) / a * a; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr size_t MAT_LDS_MAX = 160 * 1024;   // LDS of a plane block of the matrix-core transforms
 
 // ---------------------------------------------------------------------------
 // Geometry of one solve
@@ -84,6 +86,12 @@ struct Geometry {
   int64_t s3[3];     // reals of the z-spectral buffer per component (C0 only)
   int U[3];          // C0: frequencies per axis shared by the components
   int ntile_c0;      // C0: tiles of the coupled apply
+  int mat;           // spectral part on the matrix-core kernels (fm_mat.h): x forward, fused y-z planes, x inverse
+  int mkt[3][3];     // 16-row tiles of the half matrices [q][axis]
+  int mcls[3][3];    // MatClass [q][axis]
+  int mns[3];        // pencil sets of a component's plane kernel
+  int mpl[3];        // planes (blocks) of a component
+  size_t mlds[3];    // LDS bytes of a component's plane
   int wrap[3];       // axis periodic for some component (halo voxels take the periodic image)
   int sd_nt[3];      // fused stress-divergence tiles per axis (x: full-width tiles only)
   int sd_tw, sd_tny; // narrow x-remainder tiles: thread columns, tiles per z slab (0: none)
@@ -135,6 +143,64 @@ bool generic_radix(int L) {
   for (int v : r)
     if (v != 2 && v != 3 && v != 4 && v != 5 && v != 8) return true;
   return false;
+}
+
+// Slots of the two halves of an axis transform (fm_mat.h).
+inline void mat_slots(int kind, int cls, int n, int& cU, int& cV) {
+  const int h = n / 2;
+  if (cls == MC_SPLIT) { cU = (n + 1) / 2; cV = h; }
+  else if (kind == K_DFT) { cU = cV = h + 1; }
+  else if (kind == K_DCT1) { cU = h + 1; cV = (n + 1) / 2; }
+  else { cU = h; cV = (n - 1) / 2; }
+}
+
+// Shape of the matrix-core transforms of a plan, and whether its spectral
+// part runs on them: every half matrix within the compiled sizes and every
+// plane within the LDS.  They replace five passes over memory by three and
+// take any length, odd and prime ones included, at the same cost per point;
+// the products grow with the length, so the line against the wavefront
+// kernels lies where those exist for every pencil.  Measured per iteration on
+// n^3 grids (us, matrix cores / axis passes; G: some lengths have only the
+// generic axis pass):
+//   FP32 Dirichlet / Neumann  16: 47/65   32: 52/56   48: 59/70   57: 69/284 G
+//     64: 84/96   80: 111/255 G   96: 157/152   120: 205/556 G   128: 337/323
+//     160: 517/516
+//   FP64 Dirichlet / Neumann  32: 56/62   48: 75/97   57: 83/323 G
+//     64: 120/136   80: 165/297 G   96: 279/250   120: 415/712 G
+// so a plan with wavefront kernels throughout leaves the axis passes for half
+// matrices of up to three tiles (n < 94) only.  With two periodic axes the
+// planes hold complex data (twice the products, and the DFT lengths are half
+// the others' extended ones):
+//   FP32 periodic  32: 57/68   64: 96/89   80: 136/228 G   120: 214/424 G
+//   FP64 periodic  32: 63/68   64: 140/126   80: 193/255 G
+// and there the line is at two tiles (n < 62).
+void mat_geometry(Geometry& g) {
+  g.mat = 0;
+  bool fits = !g.c0, wave = true, big = false;
+  for (int a = 0; a < 3; ++a) fits = fits && g.n[a] >= 4;
+  for (int q = 0; q < 3; ++q) {
+    bool cx = false, pair = false;
+    int cU[3], cV[3];
+    for (int a = 0; a < 3; ++a) {
+      const int k = g.kinds[q][a];
+      g.mcls[q][a] = k == K_DCT3 || k == K_DST3 ? MC_SPLIT : (k == K_DFT && cx) ? MC_CPLX : MC_FOLD;
+      pair = pair || g.mcls[q][a] == MC_CPLX;
+      cx = cx || k == K_DFT;
+      g.mkt[q][a] = (g.n[a] / 2 + 1 + 15) / 16;
+      mat_slots(k, g.mcls[q][a], g.n[a], cU[a], cV[a]);
+    }
+    g.mns[q] = pair ? 2 : 1;
+    const bool xc = g.kinds[q][0] == K_DFT;
+    g.mpl[q] = xc && pair ? cU[0] : cU[0] + cV[0];
+    const int npl = xc && pair ? 2 : 1;
+    const int kt = std::max(g.mkt[q][1], g.mkt[q][2]);
+    g.mlds[q] = mat_plane_lds(npl, g.mkt[q][1], g.mkt[q][2], g.N[2], g.rbytes) * g.rbytes;
+    fits = fits && g.mkt[q][0] <= mat_max_kt(g.rbytes, 1) && g.mlds[q] <= MAT_LDS_MAX &&
+           kt <= mat_max_kt(g.rbytes, g.mns[q]);
+    for (int pass = 0; pass < 5; ++pass) wave = wave && g.wE[q][pass] != 0;
+    big = big || std::max(kt, g.mkt[q][0]) >= (pair ? 3 : 4);
+  }
+  g.mat = fits && !(wave && big);
 }
 
 int make_geometry(const fm_plan_desc* d, Geometry& g) {
@@ -231,6 +297,7 @@ int make_geometry(const fm_plan_desc* d, Geometry& g) {
         return fail(FM_E_UNSUPPORTED, "pencil too long for the LDS transform");
     }
   }
+  mat_geometry(g);
   for (int i = 0; i < 3; ++i) {
     g.wrap[i] = 0;
     for (int q = 0; q < 3; ++q) g.wrap[i] |= g.kinds[q][i] == K_DFT ? 1 : 0;
@@ -283,6 +350,7 @@ struct Layout {
       part_g, fill, tw, gtab, group, total;
   size_t tw_off[3][3];
   size_t g_off[3][3];   // green tables per comp, axis: s2 (M doubles), c2 (M doubles)
+  size_t mat_off[3][3]; // matrix-core tables per comp, axis (shared where kind, class and role agree)
   size_t group_bytes;
 };
 
@@ -322,6 +390,21 @@ inline SdivTiling sdiv_tiling(const Geometry& g, bool deep) {
   return {zc, nz, (g.sd_nt[0] * g.sd_nt[1] + g.sd_tny) * nz};
 }
 
+// Bytes of one axis' matrix-core tables: four half matrices, the slot
+// frequencies in FP64 and in the plan's precision, the cosine base table.
+struct MatBlock {
+  size_t half, gs, gz, base, total;
+};
+inline MatBlock mat_block(int kt, int n, int rbytes) {
+  MatBlock b;
+  b.half = (size_t)kt * kt * 256 * rbytes;
+  b.gs = 4 * b.half;
+  b.gz = b.gs + (size_t)64 * kt * 8;
+  b.base = b.gz + (size_t)64 * kt * rbytes;
+  b.total = align_up(b.base + (size_t)4 * n * 8);
+  return b;
+}
+
 void tiles_of(const Geometry& g, int64_t t[NWL]) {
   for (int k = 0; k < NWL; ++k) t[k] = 0;
   t[WL_VOX] = g.ntile_v;
@@ -330,6 +413,12 @@ void tiles_of(const Geometry& g, int64_t t[NWL]) {
   t[WL_C0] = g.ntile_c0;
   for (int q = 0; q < 3; ++q) {
     const int rows = g.N[1] * g.N[2];
+    if (g.mat) {
+      t[WL_PASS0 + 0] += cdiv(rows, 16 * MAT_WAVES);
+      t[WL_PASS0 + 4] += cdiv(rows, 16 * MAT_WAVES);
+      t[WL_PASS0 + 2] += g.mpl[q];
+      continue;
+    }
     t[WL_PASS0 + 0] += cdiv(rows, g.cols[q][0]);
     t[WL_PASS0 + 4] += cdiv(rows, g.cols[q][4]);
     t[WL_PASS0 + 1] += cdiv(g.M[q][0], g.cols[q][1]) * g.N[2];
@@ -379,9 +468,33 @@ void make_layout(const fm_plan_desc* d, const Geometry& g, Layout& L) {
     for (int a = 0; a < 3; ++a) L.tw_off[q][a] = take(2 * R * (size_t)g.L[q][a]);
   for (int q = 0; q < 3; ++q)
     for (int a = 0; a < 3; ++a) L.g_off[q][a] = take(16 * (size_t)g.M[q][a]);
+  if (g.mat) {
+    // matrix-core tables: in the second spectral buffer, which the plane
+    // kernel does not use, where they fit
+    size_t need = 0;
+    for (int q = 0; q < 3; ++q)
+      for (int a = 0; a < 3; ++a) {
+        bool shared = false;
+        for (int q2 = 0; q2 <= q && !shared; ++q2)
+          for (int a2 = 0; a2 < (q2 == q ? a : 3) && !shared; ++a2)
+            if (g.kinds[q2][a2] == g.kinds[q][a] && g.mcls[q2][a2] == g.mcls[q][a] && g.n[a2] == g.n[a] &&
+                (a2 == 2) == (a == 2)) {
+              L.mat_off[q][a] = L.mat_off[q2][a2];
+              shared = true;
+            }
+        if (!shared) {
+          L.mat_off[q][a] = need;
+          need += mat_block(g.mkt[q][a], g.n[a], g.rbytes).total;
+        }
+      }
+    const size_t base = need <= R * (size_t)(g.s2[0] + g.s2[1] + g.s2[2]) ? L.specB : take(need);
+    for (int q = 0; q < 3; ++q)
+      for (int a = 0; a < 3; ++a) L.mat_off[q][a] += base;
+  }
   // sized for the most tiles any transform-kernel choice can produce (one
   // column per tile), so that fm_autotune can switch kernels in place
   Geometry gmax = g;
+  gmax.mat = 0;
   for (int q = 0; q < 3; ++q)
     for (int pass = 0; pass < NPASS; ++pass) gmax.cols[q][pass] = 1;
   int64_t t[NWL];
@@ -562,7 +675,11 @@ struct fm_plan {
 // (+ 2 kind + packed) the E = 3 pencils on 64 lanes (24) and on 32 lanes
 // (34), and the E = 1 (44) and E = 2 (54) pencils on 64 lanes; buckets 1-3
 // and 21 stay empty.
-constexpr int NBUCKET = 64;
+// Matrix-core kernels: 64 + tiles - 1 for the x passes, 70 + 6 (sets - 1) +
+// tiles - 1 for the planes.
+constexpr int NBUCKET = 82;
+constexpr int B_MATX = 64, B_MATP = 70;
+inline int mat_bucket(int base, int ns, int kt) { return base + 6 * (ns - 1) + kt - 1; }
 inline int bucket_of(int E, int LN, int kind, int packed) {
   const int pk = 2 * kind + (packed ? 1 : 0);
   if (E == 3 && LN >= 32) return (LN == 64 ? 24 : 34) + pk;
@@ -572,7 +689,7 @@ inline int bucket_of(int E, int LN, int kind, int packed) {
                case 6: return 6; case 8: return 10 + 2 * kind + (packed ? 1 : 0); case 12: return 8;
                case 16: return 9; default: return 0; }
 }
-constexpr int E_of_bucket[NBUCKET] = {0, 1, 2, 3, 4, 5, 6, 8, 12, 16, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 1, 3, 1, 3,
+constexpr int E_of_bucket[B_MATX] = {0, 1, 2, 3, 4, 5, 6, 8, 12, 16, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 1, 3, 1, 3,
                                       3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3, 3,
                                       1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2};
 
@@ -663,6 +780,32 @@ void fill_pass_descs(fm_plan* p) {
       for (int i = 0; i < d.nrad; ++i) d.rad[i] = rad[i];
       d.F = g.F[q][pass];
       d.tw = ws + p->lay.tw_off[q][axis];
+      d.ctrl = (const Ctrl*)(ws + p->lay.ctrl);
+      d.pair = g.mat && g.mns[q] == 2;
+      if (g.mat)
+        for (int a = 0; a < 3; ++a) {
+          MatAxis& m = d.mx[a];
+          const int kt = g.mkt[q][a], n = g.n[a], rem = n / 2 + 1 - 16 * (kt - 1);
+          const MatBlock b = mat_block(kt, n, g.rbytes);
+          char* t = ws + p->lay.mat_off[q][a];
+          m.kind = g.kinds[q][a];
+          m.n = n;
+          m.cls = g.mcls[q][a];
+          m.kt = kt;
+          // a step covers four columns: one per lane group in the natural
+          // order (z forward, FP64 results), four apart in the quad order
+          // (all four unless one holds every column)
+          const int natural = rem <= 4 ? 1 : 4, quad = rem <= 1 ? 1 : 4;
+          m.rlf = a == 2 ? natural : quad;
+          m.rli = g.rbytes == 8 ? natural : quad;
+          mat_slots(m.kind, m.cls, n, m.cU, m.cV);
+          int cnt;
+          raw_range(m.kind, n, m.j0, cnt);
+          m.j1 = m.j0 + cnt;
+          m.fU = t; m.fV = t + b.half; m.iU = t + 2 * b.half; m.iV = t + 3 * b.half;
+          m.gs = (const double*)(t + b.gs);
+          m.gz = t + b.gz;
+        }
       switch (pass) {
         case 0:   // x forward: D ring rows -> A (M0 per row)
           d.cplx_in = 0; d.cplx_out = c1; d.packed = 1;
@@ -746,8 +889,57 @@ void fill_pass_descs(fm_plan* p) {
           d.in = Cz; d.out = B;
           break;
       }
+      if (g.mat) {
+        if (pass == 0 || pass == 4) {
+          d.cols = 16 * MAT_WAVES;
+          d.tiles_p0 = (int)cdiv(d.n_p0, d.cols);
+        } else if (pass == 2) {
+          d.in = d.out = A;
+          d.tiles_p0 = g.mpl[q];
+          d.n_p1 = 1;
+        }
+      }
     }
   }
+}
+
+// Matrix-core tables of a plan: the cosine base tables from the host (FP64
+// values of long-double cosines, exact 0 and +-1 at the quarter turns), the
+// half matrices from a kernel.
+int build_mat_tables(fm_plan* p) {
+  const Geometry& g = p->g;
+  if (!g.mat) return 0;
+  std::map<size_t, std::vector<double>> host;
+  for (int q = 0; q < 3; ++q)
+    for (int a = 0; a < 3; ++a) {
+      const size_t off = p->lay.mat_off[q][a];
+      if (host.count(off)) continue;
+      const int n = g.n[a];
+      std::vector<double>& t = host[off];
+      t.resize(4 * (size_t)n);
+      for (int m = 0; m <= n; ++m) {
+        const double v = m == n ? 0.0 : (double)cosl(M_PIl * m / (2.0L * n));
+        t[m] = v;
+        t[2 * n - m] = m == n ? 0.0 : -v;
+        t[(4 * n - m) % (4 * n)] = v;
+        t[2 * n + m] = m == n ? 0.0 : -v;
+      }
+      const MatBlock b = mat_block(g.mkt[q][a], n, g.rbytes);
+      char* d = p->ws + off;
+      HIPCHK(hipMemcpyAsync(d + b.base, t.data(), 8 * t.size(), hipMemcpyHostToDevice, p->stream));
+      MatTableArgs A;
+      A.kind = g.kinds[q][a]; A.n = n; A.cls = g.mcls[q][a]; A.kt = g.mkt[q][a]; A.natural = a == 2;
+      A.base = (const double*)(d + b.base);
+      A.s2 = (const double*)(p->ws + p->lay.g_off[q][a]);
+      A.c2 = A.s2 + g.M[q][a];
+      A.fU = d; A.fV = d + b.half; A.iU = d + 2 * b.half; A.iV = d + 3 * b.half;
+      A.gs = (double*)(d + b.gs);
+      A.gz = d + b.gz;
+      mat_build_tables(g.rbytes, A, p->stream);
+    }
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipStreamSynchronize(p->stream));     // the host tables are released on return
+  return 0;
 }
 
 int upload_tables(fm_plan* p) {
@@ -899,6 +1091,15 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
         const int di = (i * 3 + q) * NPASS + pass;
         P[di] = d;
         if (!slot_used(p->g, pass)) continue;
+        if (p->g.mat) {
+          if (pass == 1 || pass == 3) continue;
+          const Geometry& mg = p->g;
+          const int b = pass == 2 ? mat_bucket(B_MATP, mg.mns[q], std::max(mg.mkt[q][1], mg.mkt[q][2]))
+                                  : mat_bucket(B_MATX, 1, mg.mkt[q][0]);
+          for (int ty = 0; ty < d.tiles_p0; ++ty) pb[pass][b].push_back(make_int2(di, ty));
+          if (pass == 2) G.blds[pass][b] = std::max(G.blds[pass][b], mg.mlds[q]);
+          continue;
+        }
         const int64_t ntiles = pass == 0 || pass == 4 ? d.tiles_p0 : (int64_t)d.tiles_p0 * d.n_p1;
         const int pk = pass;   // launch order slot
         const int E = p->g.wE[q][pass], LN = p->g.wN[q][pass];
@@ -1138,6 +1339,7 @@ int set_lds_limits() {
   HIPCHK((set_wave_lds<R, 12>(big)));
   HIPCHK((set_wave_lds<R, 16>(big)));
   HIPCHK(set_sdiv_lds<R>());
+  HIPCHK(mat_set_limits(sizeof(R)));
   done = true;
   return 0;
 }
@@ -1219,7 +1421,13 @@ int launch_bucket(const Group& G, int pk, int b) {
   const dim3 grid((unsigned)G.bn[pk][b]);
   const size_t lds = G.blds[pk][b];
   hipStream_t st = G.stream;
-  if (b >= 24) {
+  if (b >= B_MATX) {
+    const int k = b >= B_MATP ? b - B_MATP : b - B_MATX;
+    const bool ok = b >= B_MATP
+                        ? mat_launch_plane(sizeof(R), k % 6 + 1, k / 6 + 1, grid.x, lds, st, G.P, wl)
+                        : mat_launch_x(sizeof(R), pk == 4, k % 6 + 1, grid.x, st, G.P, wl);
+    if (!ok) return fail(FM_E_INVALID_ARG, "internal: no matrix-core kernel of this size");
+  } else if (b >= 24) {
     const int set = (b - 24) / 10, kind = ((b - 24) % 10) >> 1, packed = b & 1;
     bool ok;
     switch (set) {
@@ -1252,7 +1460,7 @@ int launch_bucket(const Group& G, int pk, int b) {
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess)
     return fail(FM_E_HIP, std::string("pass launch (mode ") + std::to_string(MODE) + ", x " + std::to_string(XP) +
-                              ", E " + std::to_string(E_of_bucket[b]) + ", lds " + std::to_string(lds) +
+                              ", E " + std::to_string(b < B_MATX ? E_of_bucket[b] : 0) + ", lds " + std::to_string(lds) +
                               ", grid " + std::to_string(G.bn[pk][b]) + "): " + hipGetErrorString(err));
   return 0;
 }
@@ -1638,12 +1846,14 @@ bool apply_choice(Geometry& g, int pass, int choice) {
       h.cols[q][pass] = packed ? 2 * F : F;
     }
   }
+  h.mat = 0;
   g = h;
   return true;
 }
 
 int rebuild_plan_group(fm_plan* p) {
   fill_pass_descs(p);
+  if (int rc = build_mat_tables(p)) return rc;   // (other kernels' passes write over them)
   return build_group(*p->self, &p, 1, p->ws + p->lay.group, p->lay.group_bytes, p->stream);
 }
 
@@ -1742,6 +1952,7 @@ int fm_plan_create(const fm_plan_desc* desc, void* d_workspace, size_t ws_bytes,
   }
   fill_pass_descs(p.get());
   rc = upload_tables(p.get());
+  if (!rc) rc = build_mat_tables(p.get());
   if (rc) return rc;
   Ctrl c;
   std::memset(&c, 0, sizeof(c));
@@ -2039,9 +2250,10 @@ int fm_profile_iterations(fm_plan* p, const fm_load_step* step, int32_t n_iter, 
 
 namespace {
 // Transform choices already tuned in this process, per signature: grid,
-// per-component transform kinds, precision, scheme, Green operator.
+// per-component transform kinds, precision, scheme, Green operator.  The
+// sixth entry is 1 where the matrix-core kernels beat the five passes.
 std::mutex g_tune_mu;
-std::map<std::string, std::array<int, 5>> g_tune_cache;
+std::map<std::string, std::array<int, 6>> g_tune_cache;
 
 std::string tune_key(const fm_plan* p) {
   std::string k;
@@ -2070,7 +2282,7 @@ int fm_autotune(fm_plan* p, const fm_load_step* step, int32_t n_iter, int32_t* c
       }
       if (ms)
         for (int i = 0; i < N_TUNE * 5; ++i) ms[i] = -1.0;
-      p->g = g;
+      if (!it->second[5]) p->g = g;
       return rebuild_plan_group(p);
     }
   }
@@ -2102,11 +2314,24 @@ int fm_autotune(fm_plan* p, const fm_load_step* step, int32_t n_iter, int32_t* c
     }
   }
   Geometry g = saved;
-  std::array<int, 5> keep;
+  std::array<int, 6> keep;
+  double sum = 0;
   for (int pass = 0; pass < 5; ++pass) {
     if (best[pass] >= 0) apply_choice(g, pass, best[pass]);
     if (choice) choice[pass] = best[pass];
     keep[pass] = best[pass];
+    sum += best_ms[pass];
+  }
+  keep[5] = 0;
+  if (saved.mat) {
+    // a plan on the matrix-core kernels keeps them when they beat the fastest
+    // five passes together
+    p->g = saved;
+    int rc = rebuild_plan_group(p);
+    if (!rc) rc = profile_iterations(p, step, n_iter, tms, true);
+    if (rc) { rebuild_plan_group(p); return rc; }
+    keep[5] = tms[4] + tms[6] + tms[8] <= sum;
+    if (keep[5]) g = saved;
   }
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
