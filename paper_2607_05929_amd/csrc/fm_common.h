@@ -73,6 +73,7 @@ struct Ctrl {
   float h32[27];
   float hc32[9];
   int32_t has_trac;       // some face carries an applied traction
+  int32_t cp;             // crystal-plasticity materials: stresses from the stress pass
   // D* of the applied tractions: 2 T_q / h per [axis][face][component]
   double dstar[18];
   float dstar32[18];
@@ -113,7 +114,7 @@ struct SolveDev {
   const void* mtab;       // material table, MT_STRIDE reals per entry
   const int32_t* mlaw;    // law per material
   void* state;            // 7 * nppv * Nv reals (or null)
-  void* sig;              // plastic solves: stress of the iterate, 6 * nppv * Nv reals (or null)
+  void* sig;              // crystal plasticity: stress of the iterate, 6 * nppv * Nv reals (or null)
   Ctrl* ctrl;
   LogEntry* log;
   double* part_s;         // ntile_s * NPART_S (stress-divergence tiles)

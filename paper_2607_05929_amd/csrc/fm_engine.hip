@@ -323,6 +323,19 @@ int make_geometry(const fm_plan_desc* d, Geometry& g) {
   int64_t nzt = cdiv(g.N[2], SD_ZC);
   while (nzt < g.N[2] && sd_per_slab * nzt < want) nzt = std::min<int64_t>(2 * nzt, g.N[2]);
   g.sd_zc = (int)cdiv(g.N[2], nzt);
+  // Of the tilings no finer than that, the one whose rounds of resident
+  // blocks (two per compute unit, three of the FP32 elastic kernel) pass the
+  // fewest layers, each tile's halo layer counted.
+  // (Measured, finer tiling / this: 80^3 J2 in FP32 55 / 28 us, 64^3 elastic
+  // in FP64 32 / 22 us.  The finite-strain divergence has no halo layer and
+  // keeps the finer tiling.)
+  const int64_t slots = 256 * (g.rbytes == 4 && !d->with_state ? 3 : 2);
+  int64_t best = INT64_MAX;
+  for (int zc = g.sd_zc, z0 = zc; !d->finite_strain && zc <= std::min(SD_ZC, g.N[2]); ++zc) {
+    if (cdiv(g.N[2], cdiv(g.N[2], zc)) != zc && zc != z0) continue;   // uneven tiles
+    const int64_t cost = cdiv(sd_per_slab * cdiv(g.N[2], zc), slots) * (zc + 1);
+    if (cost < best) { best = cost; g.sd_zc = zc; }
+  }
   g.sd_nt[2] = (int)cdiv(g.N[2], g.sd_zc);
   g.ntile_s = (int)(sd_per_slab * g.sd_nt[2]);
   g.ntile_v = (int)cdiv(g.Nv, SPACE_TILE);
@@ -659,6 +672,7 @@ struct fm_plan {
   PassDesc pd[3][NPASS]{};   // host images, per component and pass slot
   bool material_set = false;
   int n_mat = 0;
+  bool has_cp = false;     // some material is crystal plasticity
   int64_t total_iters = 0;
   Group* self = nullptr;   // single-plan group
   const double* ustar_cur = nullptr;   // nodal u* folded into u^f for the current increment
@@ -695,7 +709,8 @@ constexpr int E_of_bucket[B_MATX] = {0, 1, 2, 3, 4, 5, 6, 8, 12, 16, 8, 8, 8, 8,
 
 struct Group {
   int prec = 0;
-  int plastic = 0;    // any solve with J2 / CP internal variables
+  int64_t nel = 0;    // stress-divergence tiles of solves without internal variables (first in their list)
+  int cp = 0;         // any solve with crystal-plasticity materials (stress pass)
   int trac = 0;       // some load path of the group applies tractions (real-space kernel with D*)
   bool eager = false; // launch directly, never through captured graphs
   int fs = 0;         // finite-strain solves (one formulation per group)
@@ -739,12 +754,14 @@ bool has_traction(const fm_load_step* st, int n) {
   return false;
 }
 
-// Select the real-space kernel with (t) or without the traction term; the
-// captured chunks hold one of them, so they are dropped on a change.
-void set_trac(Group& G, bool t) {
-  if (G.trac != (int)t) {
+// Select the real-space kernels: with (t) or without the traction term, with
+// (cp) or without the stress pass; the captured chunks hold one choice, so
+// they are dropped on a change.
+void set_kernels(Group& G, bool t, bool cp) {
+  if (G.trac != (int)t || G.cp != (int)cp) {
     G.drop_graphs();
     G.trac = t;
+    G.cp = cp;
   }
 }
 
@@ -1042,8 +1059,6 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
   G.drop_graphs();
   G.prec = plans[0]->d.prec;
   G.ns = ns;
-  G.plastic = 0;
-  for (int i = 0; i < ns; ++i) G.plastic |= plans[i]->d.with_state ? 1 : 0;
   G.fs = plans[0]->d.finite_strain;
   for (int i = 0; i < ns; ++i)
     if (plans[i]->d.finite_strain != G.fs) return fail(FM_E_INVALID_ARG, "a batch must share one formulation (small or finite strain)");
@@ -1139,7 +1154,13 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
       off += G.bn[k][b];
     }
   }
-  for (int k = 0; k < 4; ++k) xcd_order(wl[k], 0, wl[k].size());
+  G.nel = std::stable_partition(wl[2].begin(), wl[2].end(), [&](const int2& w) { return !S[w.x].has_state; }) -
+          wl[2].begin();
+  for (int k = 0; k < 4; ++k) {
+    const size_t cut = k == 2 ? (size_t)G.nel : 0;
+    xcd_order(wl[k], 0, cut);
+    xcd_order(wl[k], cut, wl[k].size());
+  }
   HIPCHK(hipMemcpyAsync(G.S, S.data(), sizeof(SolveDev) * ns, hipMemcpyHostToDevice, stream));
   HIPCHK(hipMemcpyAsync(G.P, P.data(), sizeof(PassDesc) * P.size(), hipMemcpyHostToDevice, stream));
   for (int k = 0; k < NWL; ++k) {
@@ -1490,9 +1511,24 @@ int launch_slot(const Group& G, int pk) {
 
 // Blocks of the FP64 real-space kernel of FP32 groups: two per compute unit,
 // walking the tile list (a multiple of 8, so each stays on one XCD).
-inline int rs64_grid(const Group& G) {
+inline int rs64_grid(int64_t n) {
   const int cu = g_num_cu > 0 ? g_num_cu : 256;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(G.nwl[WL_SDIV], 2 * cu));
+  return (int)std::max<int64_t>(1, std::min<int64_t>(n, 2 * cu));
+}
+
+// Tiles [t0, t1) of the stress-divergence list: solves without (PL = 0) or
+// with internal variables.  FP32 groups launch the FP32 and the FP64
+// kernel; each solve's control block picks the one that works (the other
+// returns).
+template <typename R, int PL, int TR>
+void launch_sdiv_range(const Group& G, int64_t t0, int64_t t1) {
+  if (t0 == t1) return;
+  const int2* wl = G.wl[WL_SDIV] + t0;
+  const int n = (int)(t1 - t0);
+  hipLaunchKernelGGL((k_sdiv<R, PL, R, TR>), dim3(n), dim3(256), sdiv_lds_bytes(sizeof(R)), G.stream, G.S, wl, n);
+  if constexpr (sizeof(R) == 4)
+    hipLaunchKernelGGL((k_sdiv<R, PL, double, TR>), dim3(rs64_grid(n)), dim3(256), sdiv_lds_bytes(8), G.stream, G.S,
+                       wl, n);
 }
 
 template <typename R, int TR>
@@ -1508,24 +1544,13 @@ int launch_sdiv(const Group& G) {
     HIPCHK(hipGetLastError());
     return 0;
   }
-  // FP32 groups launch the FP32 and the FP64 real-space kernel; each solve's
-  // control block picks the one that works (the other returns)
-  if (G.plastic) {
-    // plastic solves: the law once per voxel (one thread each), then the
-    // fused kernel reads those stresses
-    if (G.nwl[WL_VOX])
-      hipLaunchKernelGGL((k_commit<R, 1, 1>), dim3(G.nwl[WL_VOX] * (SPACE_TILE / 256)), dim3(256), 0, st, G.S,
-                         G.wl[WL_VOX]);
-    hipLaunchKernelGGL((k_sdiv<R, 1, R, TR>), dim3(nw), dim3(256), sdiv_lds_bytes(sizeof(R)), st, G.S, G.wl[WL_SDIV], nw);
-    if constexpr (sizeof(R) == 4)
-      hipLaunchKernelGGL((k_sdiv<R, 1, double, TR>), dim3(rs64_grid(G)), dim3(256), sdiv_lds_bytes(8), st, G.S,
-                         G.wl[WL_SDIV], nw);
-  } else {
-    hipLaunchKernelGGL((k_sdiv<R, 0, R, TR>), dim3(nw), dim3(256), sdiv_lds_bytes(sizeof(R)), st, G.S, G.wl[WL_SDIV], nw);
-    if constexpr (sizeof(R) == 4)
-      hipLaunchKernelGGL((k_sdiv<R, 0, double, TR>), dim3(rs64_grid(G)), dim3(256), sdiv_lds_bytes(8), st, G.S,
-                         G.wl[WL_SDIV], nw);
-  }
+  // crystal plasticity: the law once per voxel (one thread each), then the
+  // fused kernel reads those stresses
+  if (G.cp && G.nwl[WL_VOX])
+    hipLaunchKernelGGL((k_commit<R, 1, 1>), dim3(G.nwl[WL_VOX] * (SPACE_TILE / 256)), dim3(256), 0, st, G.S,
+                       G.wl[WL_VOX]);
+  launch_sdiv_range<R, 0, TR>(G, 0, G.nel);
+  launch_sdiv_range<R, 1, TR>(G, G.nel, nw);
   HIPCHK(hipGetLastError());
   return 0;
 }
@@ -1621,7 +1646,7 @@ template <typename R>
 int launch_commit_t(fm_plan* p) {
   const Group& G = *p->self;
   if (G.fs) hipLaunchKernelGGL((k_fs_out<R>), dim3(G.nwl[WL_VOX]), dim3(256), 0, G.stream, G.S, G.wl[WL_VOX]);
-  else if (G.plastic) hipLaunchKernelGGL((k_commit<R, 1>), dim3(G.nwl[WL_VOX]), dim3(256), 0, G.stream, G.S, G.wl[WL_VOX]);
+  else if (p->d.with_state) hipLaunchKernelGGL((k_commit<R, 1>), dim3(G.nwl[WL_VOX]), dim3(256), 0, G.stream, G.S, G.wl[WL_VOX]);
   else hipLaunchKernelGGL((k_commit<R, 0>), dim3(G.nwl[WL_VOX]), dim3(256), 0, G.stream, G.S, G.wl[WL_VOX]);
   HIPCHK(hipGetLastError());
   return 0;
@@ -1682,6 +1707,7 @@ int begin_step(fm_plan* p, const fm_load_step& st, int t, const Ctrl* prev) {
   c.fp32 = p->d.prec == FM_FP32_MIXED;
   c.rs64 = 0;
   c.has_trac = 0;
+  c.cp = p->has_cp;
   for (int i = 0; i < 3; ++i)
     for (int a = 0; a < 2; ++a)
       for (int q = 0; q < 3; ++q) {
@@ -2016,6 +2042,7 @@ int fm_set_material(fm_plan* p, const int32_t* d_mat_id, int32_t n_mat, const fm
   p->ustar_cur = nullptr;
   p->material_set = true;
   p->n_mat = n_mat;
+  p->has_cp = std::find(laws.begin(), laws.end(), (int32_t)LAW_CP) != laws.end();
   return FM_OK;
 }
 
@@ -2023,7 +2050,7 @@ int fm_solve(fm_plan* p, const fm_load_step* steps, int32_t n_steps, fm_outputs*
   if (!p || !steps || n_steps < 1) return fail(FM_E_INVALID_ARG, "null plan or empty load path");
   if (!p->material_set) return fail(FM_E_STATE, "fm_set_material must be called before fm_solve");
   if (int rc = check_tractions(p->d, steps, n_steps)) return rc;
-  set_trac(*p->self, has_traction(steps, n_steps));
+  set_kernels(*p->self, has_traction(steps, n_steps), p->has_cp);
   if (log) log->count = 0;
   p->total_iters = 0;
   int result = FM_OK;
@@ -2089,7 +2116,7 @@ int fm_residual(fm_plan* p, const fm_load_step* step, const double* d_uf, double
   if (!p || !step || !d_uf || !d_D) return fail(FM_E_INVALID_ARG, "null argument");
   if (!p->material_set) return fail(FM_E_STATE, "fm_set_material must be called first");
   if (int rc = check_tractions(p->d, step, 1)) return rc;
-  set_trac(*p->self, has_traction(step, 1));
+  set_kernels(*p->self, has_traction(step, 1), p->has_cp);
   int rc = begin_step(p, *step, 0, nullptr);
   if (rc) return rc;
   const int64_t n3 = 3 * p->g.Nn;
@@ -2179,7 +2206,7 @@ int profile_iterations(fm_plan* p, const fm_load_step* step, int32_t n_iter, dou
   if (!p || !step || n_iter < 1 || !ms) return fail(FM_E_INVALID_ARG, "null argument");
   if (!p->material_set) return fail(FM_E_STATE, "fm_set_material must be called first");
   if (int rc = check_tractions(p->d, step, 1)) return rc;
-  set_trac(*p->self, has_traction(step, 1));
+  set_kernels(*p->self, has_traction(step, 1), p->has_cp);
   int rc = begin_step(p, *step, 0, nullptr);
   if (rc) return rc;
   Ctrl c;

@@ -409,6 +409,39 @@ __device__ __forceinline__ const FM_GLOBAL R* zero_material() {
   else return (const FM_GLOBAL R*)k_zero_material64;
 }
 
+// J2 plasticity with linear hardening, radial return.
+template <typename R, typename PT>
+__device__ __forceinline__ void law_j2(PT P, const R eps[6], R sig[6], const R st[7], R stn[7]) {
+  const R lam = P[0], mu = P[1], sy0 = P[2], H = P[3];
+  R ee[6];
+#pragma unroll
+  for (int i = 0; i < 6; ++i) ee[i] = eps[i] - st[i];
+  const R tr = ee[0] + ee[1] + ee[2];
+  R s[6];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) sig[i] = 2 * mu * ee[i] + lam * tr;
+#pragma unroll
+  for (int i = 3; i < 6; ++i) sig[i] = 2 * mu * ee[i];
+  const R pm = (sig[0] + sig[1] + sig[2]) / 3;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) s[i] = sig[i] - (i < 3 ? pm : (R)0);
+  const R ss = s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]);
+  const R q = sqrt((R)1.5 * ss);
+  const R f = q - (sy0 + H * st[6]);
+#pragma unroll
+  for (int i = 0; i < 7; ++i) stn[i] = st[i];
+  if (f > 0) {
+    const R dp = f / (3 * mu + H);
+    const R fac = 1 - 3 * mu * dp / q;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      sig[i] = (i < 3 ? pm : (R)0) + fac * s[i];
+      stn[i] = st[i] + (R)1.5 * dp * s[i] / q;
+    }
+    stn[6] = st[6] + dp;
+  }
+}
+
 // sp: the stress of the point's previous evaluation (Voigt), a start for
 // the crystal-plasticity Newton solve, or null.
 template <typename R, typename PT>
@@ -431,34 +464,7 @@ __device__ __forceinline__ void law_eval(int law, PT P, const R eps[6], R sig[6]
 #pragma unroll
     for (int i = 0; i < 7; ++i) stn[i] = st[i];
   } else if (law == LAW_J2) {
-    const R lam = P[0], mu = P[1], sy0 = P[2], H = P[3];
-    R ee[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) ee[i] = eps[i] - st[i];
-    const R tr = ee[0] + ee[1] + ee[2];
-    R s[6];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) sig[i] = 2 * mu * ee[i] + lam * tr;
-#pragma unroll
-    for (int i = 3; i < 6; ++i) sig[i] = 2 * mu * ee[i];
-    const R pm = (sig[0] + sig[1] + sig[2]) / 3;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) s[i] = sig[i] - (i < 3 ? pm : (R)0);
-    const R ss = s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2 * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]);
-    const R q = sqrt((R)1.5 * ss);
-    const R f = q - (sy0 + H * st[6]);
-#pragma unroll
-    for (int i = 0; i < 7; ++i) stn[i] = st[i];
-    if (f > 0) {
-      const R dp = f / (3 * mu + H);
-      const R fac = 1 - 3 * mu * dp / q;
-#pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        sig[i] = (i < 3 ? pm : (R)0) + fac * s[i];
-        stn[i] = st[i] + (R)1.5 * dp * s[i] / q;
-      }
-      stn[6] = st[6] + dp;
-    }
+    law_j2<R>(P, eps, sig, st, stn);
   } else {
     R em[6], epn[6], sm[6], epm[6], G, spm[6];
     to_mandel(eps, em);

@@ -224,7 +224,7 @@ __global__ void __launch_bounds__(256, SIGMA ? 2 : 1) k_commit(const SolveDev* _
   const int2 w = work[SIGMA ? blockIdx.x / (SPACE_TILE / 256) : blockIdx.x];
   const SolveDev& s = S[w.x];
   const FM_GLOBAL Ctrl* C = gconst(s.ctrl);
-  if (SIGMA && (s.sig == nullptr || C->status != ST_RUNNING)) return;
+  if (SIGMA && (!C->cp || C->status != ST_RUNNING)) return;
   for (int sub = SIGMA ? (int)(blockIdx.x % (SPACE_TILE / 256)) : 0; sub < SPACE_TILE / 256;
        sub += SIGMA ? SPACE_TILE / 256 : 1) {
     const int64_t v = (int64_t)w.y * SPACE_TILE + sub * 256 + threadIdx.x;
@@ -497,15 +497,88 @@ __device__ __forceinline__ void node_div(const CT* __restrict__ P, int lx, int l
 // Bytes of dynamic LDS of k_sdiv.
 __host__ __device__ inline size_t sdiv_lds_bytes(int rbytes) { return (size_t)2 * 12 * SD_VT * rbytes; }
 
-// PL = 1: the group holds solves with internal variables, whose stresses
-// come from the stress pass (k_commit with SIGMA = 1); the law evaluated here
-// is elastic.  R is the storage type of the solve's fields (residual ring,
-// material table, stress buffer), CT the type the kernel computes in.  FP32
-// solves launch both the CT = float kernel and the CT = double one; the
-// control block's rs64 flag selects which of the two does the work (the
-// FP64 one once the FP32 residual has stalled at its rounding floor).
-template <typename R, int PL, typename CT, int TR>
+// Stresses of one voxel of a solve with J2 materials from its FP64 corner
+// displacements: strain and law in FP64 with the internal variables of the
+// previous increment, stress rounded to the storage type.
+// us: G (9), H (27) and the cross terms (9) of u* in LDS, read per layer.
+template <typename R, typename CT, int SCH>
+__device__ __forceinline__ void state_law_stress(const SolveDev& s, const double* us, int vx, int vy, int vz, int law,
+                                                 const FM_GLOBAL R* P, const R (&p4)[4], const double (&c8)[3][8],
+                                                 const R (&st)[2][7], CT (&sig2)[2][6]) {
+  const double xc = (vx + 0.5) * s.h, yc = (vy + 0.5) * s.h, zc = (vz + 0.5) * s.h;
+  // gradients component by component (the barriers keep the scheduler from
+  // reading all of us ahead, which would not leave registers for the rest)
+  constexpr int np = SCH == 1 ? 2 : 1;
+  const double f = (SCH == 1 ? 0.5 : 0.25) / s.h;
+  double g[2][3][3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      const double* H = us + 9 + (q * 3 + l) * 3;
+      double gs = us[q * 3 + l] + H[0] * xc + H[1] * yc;
+      gs += H[2] * zc;
+      // signed sums over the even and the odd corners
+      double t[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        bool first = true;
+        t[r] = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (((c ^ (c >> 1) ^ (c >> 2)) & 1) != r) continue;
+          const double v = ((c >> l) & 1) ? c8[q][c] : -c8[q][c];
+          t[r] = first ? v : t[r] + v;
+          first = false;
+        }
+      }
+      if constexpr (SCH == 1) {
+        const double hc = us[36 + l * 3 + q];
+        g[0][l][q] = t[0] * f + gs - hc;
+        g[1][l][q] = t[1] * f + gs + hc;
+      } else {
+        g[0][l][q] = (t[0] + t[1]) * f + gs;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < np; ++r) {
+    __builtin_amdgcn_sched_barrier(0);
+    double eps[6], sd[6], a[7], b[7];
+    eps[0] = g[r][0][0]; eps[1] = g[r][1][1]; eps[2] = g[r][2][2];
+    eps[3] = 0.5 * (g[r][1][2] + g[r][2][1]);
+    eps[4] = 0.5 * (g[r][0][2] + g[r][2][0]);
+    eps[5] = 0.5 * (g[r][0][1] + g[r][1][0]);
+#pragma unroll
+    for (int k = 0; k < 7; ++k) a[k] = st[r][k];
+    if (law == LAW_J2) law_j2<double>(p4, eps, sd, a, b);
+    else if (law == LAW_ISO) law_elastic<double>(LAW_ISO, p4, eps, sd, a, b);
+    else law_elastic<double>(LAW_ANISO, P, eps, sd, a, b);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sig2[r][k] = (CT)(R)sd[k];
+  }
+}
+
+// R is the storage type of the solve's fields (residual ring, material
+// table, stress buffer), CT the type the kernel computes in.  FP32 solves
+// launch both the CT = float kernel and the CT = double one; the control
+// block's rs64 flag selects which of the two does the work (the FP64 one once
+// the FP32 residual has stalled at its rounding floor).  MODE: the source of
+// the stresses, fixed at compile time so that every load of a layer is
+// unconditional and a wait for one leaves the later ones in flight.
+//   SD_ELASTIC  elastic laws (CT = double; sdiv_tile_f32 otherwise)
+//   SD_HEX1, SD_TETRA2  a solve with internal variables: strain and law in
+//       FP64 (law_eval_e64).  Evaluating them here instead of in a stress
+//       pass saves writing and reading the stresses, and the crystal
+//       plasticity code its registers (192^3 HEX1 in FP32: 245 us, the stress
+//       pass and its reader 447 + 162 us; 80^3: 28 against 69 us).
+//   SD_BUFFER   crystal plasticity, stresses from the stress pass: the law
+//       costs too much to evaluate again on the halo of every tile.
+enum SdMode : int { SD_ELASTIC = 0, SD_HEX1 = 1, SD_TETRA2 = 2, SD_BUFFER = 3 };
+template <typename R, int MODE, typename CT, int TR>
 __device__ __forceinline__ void sdiv_tile(const SolveDev* __restrict__ S, const int2 w) {
+  static_assert(MODE != SD_ELASTIC || sizeof(CT) == 8, "FP32 elastic tiles are sdiv_tile_f32");
   const SolveDev& s = S[w.x];
   const FM_GLOBAL Ctrl* C = gconst(s.ctrl);
   if (C->status != ST_RUNNING) return;
@@ -528,21 +601,9 @@ __device__ __forceinline__ void sdiv_tile(const SolveDev* __restrict__ S, const 
   // per-thread partials in CT (each thread sums at most 2 (sd_zc + 1) points),
   // FP64 across the block
   CT acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  // u* gradient of this voxel column: gA + gB z_c.  FP32: from the uniform
-  // FP32 copies in the control block (gB and the cross terms stay scalar).
+  // u* gradient of this voxel column: gA + gB z_c
   CT gA[3][3], gB[3][3], hc[3][3];
-  if constexpr (sizeof(CT) == 4) {
-    // read before any store, so that the uniform values can live in scalars
-    const float xc = (float)((vx + 0.5) * s.h), yc = (float)((vy + 0.5) * s.h);
-#pragma unroll
-    for (int l = 0; l < 3; ++l)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        gA[l][q] = C->g32[q * 3 + l] + C->h32[(q * 3 + l) * 3] * xc + C->h32[(q * 3 + l) * 3 + 1] * yc;
-        gB[l][q] = C->h32[(q * 3 + l) * 3 + 2];
-        hc[l][q] = C->hc32[l * 3 + q];
-      }
-  } else {
+  if constexpr (MODE == SD_ELASTIC) {
     ustar_grad_column<CT>(s, C, vx, vy, gA, gB);
     tet_cross_terms<CT>(s, C, hc);
   }
@@ -557,104 +618,141 @@ __device__ __forceinline__ void sdiv_tile(const SolveDev* __restrict__ S, const 
   // x-y mirror drops occur only on the faces of axes periodic for another
   // component: waves without any take the plain four-column sums
   const bool wave_drop = __any(nxy.drop != 0);
-  // plastic solves read the stresses of the per-voxel stress pass
-  const bool from_buf = PL && s.sig != nullptr;
-  // FP32 corner carry: top corner 4 (FP64) and corners 5-7 minus it, per component
-  double cu4[3] = {0, 0, 0};
-  CT cdt[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  int vz_prev = -2;
+  constexpr bool from_buf = MODE == SD_BUFFER, state_law = MODE == SD_HEX1 || MODE == SD_TETRA2;
+  constexpr int NPS = MODE == SD_TETRA2 ? 2 : 1;
+  constexpr bool ahead = sizeof(CT) == 4;   // registers for the next layer's loads
+  __shared__ double us[45];
+  if constexpr (state_law) {
+    const int i = threadIdx.x;
+    if (i < 9) us[i] = C->G[i];
+    else if (i < 36) us[i] = C->H[i - 9];
+    else if (i < 45) {
+      const int l = (i - 36) / 3, q = (i - 36) % 3;
+      us[i] = (s.scheme == 1 ? 0.5 * s.h : 0.0) * C->H[(q * 3 + (l == 0 ? 1 : 0)) * 3 + (l == 2 ? 1 : 2)];
+    }
+    __syncthreads();
+  }
+  // Solves with internal variables: the top face and the internal variables
+  // of a layer's voxel are loaded while the layer before is computed (FP32;
+  // in FP64 with the layer itself), its law and parameters ahead of those; the bottom face is the previous layer's
+  // top face where the layers are adjacent.  (Elastic solves load all eight
+  // corners of the layer: with the stiffness there are no registers for more.)
+  const FM_GLOBAL double* uc = gconst(s.uf) + (int64_t)vy * s.N[0] + vx;
+  double face[3][4], top[3][4];
+  R stn[2][7];
+  auto load_face = [&](int j, double (&t)[3][4]) {
+    const FM_GLOBAL double* b = uc + (int64_t)j * s.N[0] * s.N[1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) t[q][c] = b[q * s.Nn + (c & 1) + (c >> 1) * s.N[0]];
+  };
+  auto load_state = [&](int vz) {
+    if constexpr (state_law) {
+      const FM_GLOBAL R* b = gconst((const R*)s.state) + ((int64_t)vz * n1 + vy) * n0 + vx;
+#pragma unroll
+      for (int r = 0; r < NPS; ++r)
+#pragma unroll
+        for (int k = 0; k < 7; ++k) stn[r][k] = b[((int64_t)k * NPS + r) * s.Nv];
+    }
+  };
+  const FM_GLOBAL R* mtab = gconst((const R*)s.mtab);
+  int law = 0;
+  CT cv[state_law || from_buf ? 1 : 21];
+  R p4[4];
+  auto load_law = [&](int z, int mt) {
+    // halo voxels across faces of axes periodic for no component hold zero
+    // stress: their elastic law reads the all-zero entry
+    const bool zero = MODE == SD_ELASTIC && (zero_xy || (!s.wrap[2] && (z < 0 || z >= n2)));
+    const FM_GLOBAL R* P = zero ? zero_material<R>() : mtab + (int64_t)mt * MT_STRIDE;
+    if constexpr (MODE == SD_ELASTIC) {
+#pragma unroll
+      for (int k = 0; k < 21; ++k) cv[k] = (CT)P[MT_VOIGT + k];
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) p4[k] = P[k];
+    }
+    law = gconst(s.mlaw)[mt];
+  };
+  auto mat_of = [&](int z) { return (int)mat[((int64_t)map_vox(z, n2, s.wrap[2]) * n1 + vy) * n0 + vx]; };
+  int vz_prev = map_vox(Z0 - 1, n2, s.wrap[2]) - 1;
+  int mt_cur = mat_of(Z0 - 1);
+  if constexpr (state_law) {
+    load_face(vz_prev + 1, face);
+    if constexpr (ahead) load_face(vz_prev + 2, top);
+    if constexpr (ahead) load_state(vz_prev + 1);
+  }
+  int mt_next = mat_of(Z0);
   const int64_t N01 = (int64_t)s.N[0] * s.N[1];
   FM_GLOBAL R* Dcol = gmut((R*)s.Dring) + (int64_t)(C->m % s.depth) * 3 * s.Nn + (int64_t)J1 * s.N[0] + J0;
-  int mt_cur = mat[((int64_t)map_vox(Z0 - 1, n2, s.wrap[2]) * n1 + vy) * n0 + vx];
   for (int zl = Z0 - 1; zl < Z1; ++zl) {
-    // material of the next voxel layer, fetched one layer ahead
-    // (unconditional: the last layer reads a valid voxel it does not use, so the
-    // load needs no branch and its wait can sink to the end of the layer)
-    const uint16_t mt_next = mat[((int64_t)map_vox(zl + 1, n2, s.wrap[2]) * n1 + vy) * n0 + vx];
     {
       const int vz = map_vox(zl, n2, s.wrap[2]);
-      const int law = gconst(s.mlaw)[mt_cur];
-      // halo voxels across faces of axes periodic for no component hold zero
-      // stress: their elastic law reads the all-zero entry
       const bool zero_halo = zero_xy || (!s.wrap[2] && (zl < 0 || zl >= n2));
-      const FM_GLOBAL R* P = (!from_buf && zero_halo) ? zero_material<R>()
-                                                      : gconst((const R*)s.mtab) + (int64_t)mt_cur * MT_STRIDE;
-      CT eps[2][6];
-      if (!from_buf) {
-        CT u[3][8], gs[3][3];
-        if constexpr (sizeof(CT) == 4) {
-          // FP32: FP64 differences to corner 0, with the bottom face taken
-          // from the previous layer's top face when the layers are adjacent
-          // (its differences to its own corner 0 formed from the rounded
-          // top-face differences)
-          const bool carry = zl >= Z0 && vz == vz_prev + 1;
-          const int64_t base = (int64_t)vz * N01 + (int64_t)vy * s.N[0] + vx;
-#pragma unroll
-          for (int q = 0; q < 3; ++q) {
-            const FM_GLOBAL double* uq = gconst(s.uf) + q * s.Nn + base;
-            double u0;
-            if (carry) {
-              u0 = cu4[q];
-#pragma unroll
-              for (int c = 1; c < 4; ++c) u[q][c] = cdt[q][c - 1];
-            } else {
-              u0 = uq[0];
-#pragma unroll
-              for (int c = 1; c < 4; ++c) u[q][c] = (CT)(uq[(c & 1) + (c >> 1) * s.N[0]] - u0);
-            }
-            u[q][0] = 0;
-            double top[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) top[c] = uq[(c & 1) + (c >> 1) * s.N[0] + N01];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) u[q][4 + c] = (CT)(top[c] - u0);
-            cu4[q] = top[0];
-#pragma unroll
-            for (int c = 1; c < 4; ++c) cdt[q][c - 1] = u[q][4 + c] - u[q][4];
-          }
+      CT sig2[2][6];   // stresses of the voxel's points
+      if constexpr (!from_buf) {
+        if constexpr (state_law) {
+          if constexpr (ahead) load_law(zl, mt_cur);
+          if (vz != vz_prev + 1) load_face(vz, face);
+          if constexpr (!ahead) { load_face(vz + 1, top); load_state(vz); }
           vz_prev = vz;
+          double c8[3][8];
+          R st[2][7];
+#pragma unroll
+          for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              c8[q][c] = face[q][c];
+              face[q][c] = c8[q][4 + c] = top[q][c];
+            }
+#pragma unroll
+          for (int r = 0; r < NPS; ++r)
+#pragma unroll
+            for (int k = 0; k < 7; ++k) st[r][k] = stn[r][k];
+          if constexpr (ahead) {   // (the last layer reads valid data it does not use)
+            const int vn = map_vox(zl + 1, n2, s.wrap[2]);
+            load_face(vn + 1, top);
+            load_state(vn);
+          }
+          if constexpr (!ahead) {
+            __builtin_amdgcn_sched_barrier(0);
+            load_law(zl, mt_cur);
+          }
+          state_law_stress<R, CT, MODE == SD_TETRA2>(s, us, vx, vy, vz, law, mtab + (int64_t)mt_cur * MT_STRIDE, p4, c8,
+                                                     st, sig2);
         } else {
+          CT u[3][8], gs[3][3], eps[2][6];
           voxel_corners<CT>(s, vx, vy, vz, u);
+          const CT zc = (CT)((vz + 0.5) * s.h);
+#pragma unroll
+          for (int l = 0; l < 3; ++l)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) gs[l][q] = gA[l][q] + gB[l][q] * zc;
+          strain_from_corners<CT, true>(s, u, gs, hc, eps);
+          load_law(zl, mt_cur);
+          if (s.nppv == 2) law_elastic_pts_eng<CT, 2>(law, cv, eps, sig2);
+          else law_elastic_pts_eng<CT, 1>(law, cv, eps, sig2);
         }
-        const CT zc = (CT)((vz + 0.5) * s.h);
-#pragma unroll
-        for (int l = 0; l < 3; ++l)
-#pragma unroll
-          for (int q = 0; q < 3; ++q) gs[l][q] = gA[l][q] + gB[l][q] * zc;
-        strain_from_corners<CT, true>(s, u, gs, hc, eps);
       }
-      // the Voigt stiffness of the voxel (read for every law, outside the
-      // law's branch, so that the loads issue together)
-      CT cv[21];
-      if (!from_buf) {
-#pragma unroll
-        for (int k = 0; k < 21; ++k) cv[k] = (CT)P[MT_VOIGT + k];
-      }
+      mt_cur = mt_next;
+      mt_next = mat_of(zl + 2);
       const int64_t v = ((int64_t)vz * n1 + vy) * n0 + vx;
       const bool own = own_xy && zl >= Z0 && zl < n2;
-      // the stresses of the voxel's points (one law branch per voxel, so the
-      // material entry is read once for both points)
-      CT sig2[2][6];
-      if (from_buf) {
+      if constexpr (from_buf) {
 #pragma unroll
         for (int r = 0; r < 2; ++r)
           if (r < s.nppv)
 #pragma unroll
             for (int k = 0; k < 6; ++k) sig2[r][k] = gconst((const R*)s.sig)[((int64_t)k * s.nppv + r) * s.Nv + v];
-      } else if (s.nppv == 2) {
-        // solves without internal variables: elastic laws only
-        law_elastic_pts_eng<CT, 2>(law, cv, eps, sig2);
-      } else {
-        law_elastic_pts_eng<CT, 1>(law, cv, eps, sig2);
       }
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         if (r >= s.nppv) break;
         const CT (&sig)[6] = sig2[r];
-        // (stresses read from the stress buffer are zeroed here)
+        // (the elastic laws give zero on the all-zero entry)
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
-          const CT val = (from_buf && zero_halo) ? (CT)0 : sig[k];
+          const CT val = (MODE != SD_ELASTIC && zero_halo) ? (CT)0 : sig[k];
           scur[0][k] = r == 0 ? val : scur[0][k];
           scur[1][k] = r == 0 ? val : (r == 1 ? val : scur[1][k]);
         }
@@ -696,7 +794,6 @@ __device__ __forceinline__ void sdiv_tile(const SolveDev* __restrict__ S, const 
     for (int r = 0; r < 2; ++r)
 #pragma unroll
       for (int k = 0; k < 6; ++k) sprev[r][k] = scur[r][k];
-    mt_cur = mt_next;
   }
   __shared__ double outp[8];
   double accd[8];
@@ -899,6 +996,19 @@ __device__ __forceinline__ void sdiv_tile_f32(const SolveDev* __restrict__ S, co
   if (threadIdx.x < 8) gmut(s.part_s)[(int64_t)w.y * NPART_S + threadIdx.x] = outp[threadIdx.x];
 }
 
+// PL = 1: solves with internal variables.
+template <typename R, int PL, typename CT, int TR>
+__device__ __forceinline__ void sdiv_any(const SolveDev* __restrict__ S, const int2 w) {
+  if constexpr (PL == 0) {
+    sdiv_tile<R, SD_ELASTIC, CT, TR>(S, w);
+  } else {
+    const SolveDev& s = S[w.x];
+    if (gconst(s.ctrl)->cp) sdiv_tile<R, SD_BUFFER, CT, TR>(S, w);
+    else if (s.scheme == 1) sdiv_tile<R, SD_TETRA2, CT, TR>(S, w);
+    else sdiv_tile<R, SD_HEX1, CT, TR>(S, w);
+  }
+}
+
 // The FP64 variant of an FP32 group is launched every iteration but works
 // only for solves near their FP32 rounding floor: it runs as a few blocks
 // per compute unit walking the tile list, so that it costs a short dispatch
@@ -910,7 +1020,7 @@ __device__ __forceinline__ void sdiv_tile_f32(const SolveDev* __restrict__ S, co
 // TR = 1 adds the applied-traction term D* at the loaded faces (groups whose
 // load paths carry tractions; the common kernel carries no traction code).
 template <typename R, int PL, typename CT = R, int TR = 0>
-__global__ void __launch_bounds__(256, sizeof(CT) == 8 ? 1 : (sizeof(R) == 4 && PL == 0 ? 3 : 4))
+__global__ void __launch_bounds__(256, PL != 0 ? 2 : sizeof(CT) == 8 ? 1 : 3)
     k_sdiv(const SolveDev* __restrict__ S, const int2* __restrict__ work, int nwork) {
   if constexpr (sizeof(R) == 4 && sizeof(CT) == 4 && PL == 0) {
     sdiv_tile_f32<R, TR>(S, work[blockIdx.x]);
@@ -930,13 +1040,13 @@ __global__ void __launch_bounds__(256, sizeof(CT) == 8 ? 1 : (sizeof(R) == 4 && 
       __syncthreads();
       const int nt = ntodo;
       for (int k = 0; k < nt; ++k) {
-        sdiv_tile<R, PL, CT, TR>(S, todo[k]);
+        sdiv_any<R, PL, CT, TR>(S, todo[k]);
         __syncthreads();
       }
       __syncthreads();   // every thread has read ntodo before the next reset
     }
   } else {
-    sdiv_tile<R, PL, CT, TR>(S, work[blockIdx.x]);
+    sdiv_any<R, PL, CT, TR>(S, work[blockIdx.x]);
   }
 }
 
