@@ -710,6 +710,7 @@ constexpr int E_of_bucket[B_MATX] = {0, 1, 2, 3, 4, 5, 6, 8, 12, 16, 8, 8, 8, 8,
 struct Group {
   int prec = 0;
   int64_t nel = 0;    // stress-divergence tiles of solves without internal variables (first in their list)
+  int npt = 1;        // most integration points per voxel of its solves
   int cp = 0;         // any solve with crystal-plasticity materials (stress pass)
   int trac = 0;       // some load path of the group applies tractions (real-space kernel with D*)
   bool eager = false; // launch directly, never through captured graphs
@@ -1059,6 +1060,8 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
   G.drop_graphs();
   G.prec = plans[0]->d.prec;
   G.ns = ns;
+  G.npt = 1;
+  for (int i = 0; i < ns; ++i) G.npt = std::max(G.npt, plans[i]->g.nppv);
   G.fs = plans[0]->d.finite_strain;
   for (int i = 0; i < ns; ++i)
     if (plans[i]->d.finite_strain != G.fs) return fail(FM_E_INVALID_ARG, "a batch must share one formulation (small or finite strain)");
@@ -1544,11 +1547,11 @@ int launch_sdiv(const Group& G) {
     HIPCHK(hipGetLastError());
     return 0;
   }
-  // crystal plasticity: the law once per voxel (one thread each), then the
-  // fused kernel reads those stresses
+  // crystal plasticity: the law once per integration point, then the fused
+  // kernel reads those stresses
   if (G.cp && G.nwl[WL_VOX])
-    hipLaunchKernelGGL((k_commit<R, 1, 1>), dim3(G.nwl[WL_VOX] * (SPACE_TILE / 256)), dim3(256), 0, st, G.S,
-                       G.wl[WL_VOX]);
+    hipLaunchKernelGGL((k_stress<R>), dim3(G.nwl[WL_VOX] * (SPACE_TILE / 64) * G.npt), dim3(64), 0, st, G.S,
+                       G.wl[WL_VOX], G.npt);
   launch_sdiv_range<R, 0, TR>(G, 0, G.nel);
   launch_sdiv_range<R, 1, TR>(G, G.nel, nw);
   HIPCHK(hipGetLastError());

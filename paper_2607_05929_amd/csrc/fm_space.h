@@ -11,6 +11,8 @@
 //            Continuous_der_symmetry_per on the stress columns; for TETRA2
 //            the reflection exchanges the two tetrahedra); FP64 block
 //            partials of sum_ip w |sigma|^2, sum sigma and sum |D|^2.
+//  k_stress  stress pass of crystal-plasticity solves (one integration point
+//            per thread), read by k_sdiv.
 //  k_commit  voxel kernel of the end of an increment: internal variables,
 //            FP64 strain / stress outputs.
 //  k_gram    Gram matrix of the residual history (Anderson, FP64 partials).
@@ -215,18 +217,13 @@ __device__ __forceinline__ void voxel_strain(const SolveDev& s, const FM_GLOBAL 
 
 // Commit of an increment: behaviour law with the converged strain, internal
 // variables stored, FP64 strain / stress outputs.  PL = 0 compiles the
-// elastic laws only, PL = 1 all laws.  SIGMA = 1 is the stress pass of an
-// iteration of a plastic solve instead: one voxel per thread (four blocks
-// per voxel tile), the law with the internal variables of the previous
-// increment, the stress into the solve's stress buffer, nothing else written.
-template <typename R, int PL, int SIGMA = 0>
-__global__ void __launch_bounds__(256, SIGMA ? 2 : 1) k_commit(const SolveDev* __restrict__ S, const int2* __restrict__ work) {
-  const int2 w = work[SIGMA ? blockIdx.x / (SPACE_TILE / 256) : blockIdx.x];
+// elastic laws only, PL = 1 all laws.
+template <typename R, int PL>
+__global__ void __launch_bounds__(256) k_commit(const SolveDev* __restrict__ S, const int2* __restrict__ work) {
+  const int2 w = work[blockIdx.x];
   const SolveDev& s = S[w.x];
   const FM_GLOBAL Ctrl* C = gconst(s.ctrl);
-  if (SIGMA && (!C->cp || C->status != ST_RUNNING)) return;
-  for (int sub = SIGMA ? (int)(blockIdx.x % (SPACE_TILE / 256)) : 0; sub < SPACE_TILE / 256;
-       sub += SIGMA ? SPACE_TILE / 256 : 1) {
+  for (int sub = 0; sub < SPACE_TILE / 256; ++sub) {
     const int64_t v = (int64_t)w.y * SPACE_TILE + sub * 256 + threadIdx.x;
     if (v >= s.Nv) continue;
     const int n0 = s.n[0], n1 = s.n[1];
@@ -271,11 +268,6 @@ __global__ void __launch_bounds__(256, SIGMA ? 2 : 1) k_commit(const SolveDev* _
       } else {
         law_elastic<R>(law, P, er, sig, st, stn);
       }
-      if (SIGMA) {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) gmut((R*)s.sig)[((int64_t)k * s.nppv + r) * s.Nv + v] = sig[k];
-        continue;
-      }
       if (PL && s.has_state && (law == LAW_J2 || law == LAW_CP)) {
 #pragma unroll
         for (int k = 0; k < 7; ++k) state[((int64_t)k * s.nppv + r) * s.Nv + v] = stn[k];
@@ -290,6 +282,50 @@ __global__ void __launch_bounds__(256, SIGMA ? 2 : 1) k_commit(const SolveDev* _
       }
     }
   }
+}
+
+// Stress pass of an iteration of a crystal-plasticity solve: the law with the
+// internal variables of the previous increment, the stress into the solve's
+// stress buffer.  The Newton solve is one long serial chain (thousands of
+// FP64 operations per point at two waves per SIMD) and its time that of the
+// slowest lane of a wave, so each thread takes one integration point and each
+// block is one wave of points of one kind: a TETRA2 grid gives twice the
+// waves of one thread per voxel, and a small one spreads over all compute
+// units (32^3 TETRA2: 127 us one thread
+// per voxel in blocks of 256, 76 us so).
+template <typename R>
+__global__ void __launch_bounds__(64, 2) k_stress(const SolveDev* __restrict__ S, const int2* __restrict__ work,
+                                                  int npt) {
+  constexpr int SUB = SPACE_TILE / 64;
+  const int2 w = work[blockIdx.x / (SUB * npt)];
+  const int part = (int)(blockIdx.x % (SUB * npt)), r = part / SUB;
+  const SolveDev& s = S[w.x];
+  const FM_GLOBAL Ctrl* C = gconst(s.ctrl);
+  if (!C->cp || C->status != ST_RUNNING || r >= s.nppv) return;
+  const int64_t v = (int64_t)w.y * SPACE_TILE + (part % SUB) * 64 + threadIdx.x;
+  if (v >= s.Nv) return;
+  const int n0 = s.n[0], n1 = s.n[1];
+  const int x = (int)(v % n0);
+  const int64_t t = v / n0;
+  const int y = (int)(t % n1), z = (int)(t / n1);
+  const int mt = gconst(s.mat)[v];
+  const int law = gconst(s.mlaw)[mt];
+  const FM_GLOBAL R* P = gconst((const R*)s.mtab) + (int64_t)mt * MT_STRIDE;
+  FM_GLOBAL R* sg = gmut((R*)s.sig) + (int64_t)r * s.Nv + v;
+  const FM_GLOBAL R* state = gconst((const R*)s.state) + (int64_t)r * s.Nv + v;
+  const int64_t str = (int64_t)s.nppv * s.Nv;
+  R st[7], stn[7], sp[6], sig[6];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) st[k] = state[k * str];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) sp[k] = sg[k * str];
+  double eps[2][6], er[6];
+  voxel_strain<double>(s, C, x, y, z, eps);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) er[k] = r == 0 ? eps[0][k] : eps[1][k];
+  law_eval_e64<R>(law, P, er, sig, st, stn, C->dt, law == LAW_CP ? sp : nullptr);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) sg[k * str] = sig[k];
 }
 
 // ---------------------------------------------------------------------------
