@@ -24,7 +24,7 @@ def build(verbose: bool = False) -> str:
     # one compiler per source, side by side, then one link
     objs, jobs = [], []
     for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
+        obj = os.path.join(HERE, src.replace(".hip", ".o"))
         cmd = [HIPCC] + FLAGS + ["-I", os.path.join(HERE, "..", "include"), "-c", "-o", obj, os.path.join(CSRC, src)]
         if verbose:
             print(" ".join(cmd), flush=True)

@@ -317,8 +317,7 @@ int make_geometry(const fm_plan_desc* d, Geometry& g) {
   // Layers per tile: at most SD_ZC, the node layers split evenly over the
   // z tiles; the number of z tiles doubles while the grid gives fewer than
   // 8 blocks per compute unit.  Each tile recomputes one voxel layer below
-  // it, so fewer layers cost more law evaluations (elastic ones: plastic
-  // solves read their stresses from the stress pass) but fill the GPU on
+  // it, so fewer layers cost more law evaluations but fill the GPU on
   // small grids; even tiles keep the last one from being a near-empty
   // block that still pays for its halo layer.
   const int64_t want = SD_WANT_BLOCKS;

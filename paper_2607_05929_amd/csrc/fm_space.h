@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(64, 2) k_stress(const SolveDev* __restrict__ S
 // that there are enough blocks to fill the GPU).
 // It marches up the layers: for voxel layer z it evaluates the behaviour law
 // on the 32 x 8 voxels that touch the tile (one per thread, the tile plus a
-// one-voxel halo; plastic solves read them from their per-voxel stress pass
+// one-voxel halo; crystal plasticity reads them from its stress pass
 // instead), sums each voxel column's contributions of layers z-1 and z into
 // LDS partials, then forms the divergence at node layer z.  The stress of an
 // elastic solve never goes to memory.  Outside the grid a halo voxel holds the periodic image
