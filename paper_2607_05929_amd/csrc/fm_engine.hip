@@ -2022,6 +2022,9 @@ int fm_set_material(fm_plan* p, const int32_t* d_mat_id, int32_t n_mat, const fm
     }
   }
   char* ws = p->ws;
+  // (with the law table, so that the two agree where a later check refuses the
+  // map: the kernels are chosen by it)
+  p->has_cp = std::find(laws.begin(), laws.end(), (int32_t)LAW_CP) != laws.end();
   HIPCHK(hipMemcpyAsync(ws + p->lay.mlaw, laws.data(), 4 * n_mat, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipMemcpyAsync(ws + p->lay.mtab, tab.data(), tab.size(), hipMemcpyHostToDevice, p->stream));
   int* bad = (int*)(ws + p->lay.part_d);   // scratch word
@@ -2044,7 +2047,6 @@ int fm_set_material(fm_plan* p, const int32_t* d_mat_id, int32_t n_mat, const fm
   p->ustar_cur = nullptr;
   p->material_set = true;
   p->n_mat = n_mat;
-  p->has_cp = std::find(laws.begin(), laws.end(), (int32_t)LAW_CP) != laws.end();
   return FM_OK;
 }
 
