@@ -281,8 +281,10 @@ int make_geometry(const fm_plan_desc* d, Geometry& g) {
       const bool packed = axis == 0 ? true : !g.cplx[q][axis - 1];
       int LN;
       const int E = wave_shape(L, LN);
-      // wavefront kernels address a component's buffers with 32-bit byte offsets
-      const int64_t comp_bytes = std::max(std::max({g.s1[q], g.s2[q], g.s3[q]}) * (int64_t)g.rbytes, g.Nn * (int64_t)8);
+      // wavefront kernels address a component's buffers with 32-bit byte
+      // offsets (the z spectrum is the buffer of slots 5 and 6 only)
+      const int64_t reals = std::max({g.s1[q], g.s2[q], pass >= 5 ? g.s3[q] : (int64_t)0});
+      const int64_t comp_bytes = std::max(reals * (int64_t)g.rbytes, g.Nn * (int64_t)8);
       g.wE[q][pass] = (E && comp_bytes < ((int64_t)1 << 32)) ? E : 0;
       g.wN[q][pass] = E ? LN : 64;
       if (g.wE[q][pass]) {
