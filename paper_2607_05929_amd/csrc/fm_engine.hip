@@ -145,6 +145,11 @@ bool generic_radix(int L) {
   return false;
 }
 
+// Pass slots: x fwd, y fwd, fused z, y inv, x inv, and for C0 plans z fwd and
+// z inv.
+constexpr int NPASS = 7;
+inline int slot_axis(int pass) { return pass == 0 || pass == 4 ? 0 : (pass == 1 || pass == 3 ? 1 : 2); }
+
 // Slots of the two halves of an axis transform (fm_mat.h).
 inline void mat_slots(int kind, int cls, int n, int& cU, int& cV) {
   const int h = n / 2;
@@ -168,15 +173,30 @@ inline void mat_slots(int kind, int cls, int n, int& cU, int& cV) {
 //   FP64 Dirichlet / Neumann  32: 56/62   48: 75/97   57: 83/323 G
 //     64: 120/136   80: 165/297 G   96: 279/250   120: 415/712 G
 // so a plan with wavefront kernels throughout leaves the axis passes for half
-// matrices of up to three tiles (n < 94) only.  With two periodic axes the
+// matrices of up to three tiles (n < 96) only.  With two periodic axes the
 // planes hold complex data (twice the products, and the DFT lengths are half
 // the others' extended ones):
 //   FP32 periodic  32: 57/68   64: 96/89   80: 136/228 G   120: 214/424 G
 //   FP64 periodic  32: 63/68   64: 140/126   80: 193/255 G
-// and there the line is at two tiles (n < 62).
+// and there the line is at two tiles (n < 64).
+//
+// A single axis of fewer than 16 cells without a wavefront kernel costs the
+// axis passes little, and two kinds of plan with complex planes past those
+// lines keep them: x is that axis (few planes, each with both parts of its
+// data to take through y and z: most compute units idle), unless y or z has
+// 48 cells, or in FP64 more planes than compute units (an incomplete second
+// round) with at least 32 cells on the other axis.  Per iteration, matrix
+// cores / axis passes, over 207 such grids 0.92 to 1.25, mean 1.07:
+//   6 x 64 x 64 periodic  FP32 90/80 us, FP64 104/85
+//   5 x 96 x 96 periodic  FP32 113/103   4 x 64 x 32 periodic  FP64 79/66
+//   96 x 64 x 5, y and z periodic  FP64 115/98
+// The rest of the grids with one such axis stays on the matrix cores (real
+// planes 5 x 96 x 96 FP32 0.79, FP64 0.85, but 96 x 5 x 96 FP64 1.05; 64 x 7
+// x 64 periodic 0.88 and 0.99; 10 x 64 x 48 periodic 0.90 and 0.97).
 void mat_geometry(Geometry& g) {
   g.mat = 0;
-  bool fits = !g.c0, wave = true, big = false;
+  bool fits = !g.c0, big = false, anypair = false, xpair = true;
+  int planes = 0;
   for (int a = 0; a < 3; ++a) fits = fits && g.n[a] >= 4;
   for (int q = 0; q < 3; ++q) {
     bool cx = false, pair = false;
@@ -197,16 +217,24 @@ void mat_geometry(Geometry& g) {
     g.mlds[q] = mat_plane_lds(npl, g.mkt[q][1], g.mkt[q][2], g.N[2], g.rbytes) * g.rbytes;
     fits = fits && g.mkt[q][0] <= mat_max_kt(g.rbytes, 1) && g.mlds[q] <= MAT_LDS_MAX &&
            kt <= mat_max_kt(g.rbytes, g.mns[q]);
-    for (int pass = 0; pass < 5; ++pass) wave = wave && g.wE[q][pass] != 0;
     big = big || std::max(kt, g.mkt[q][0]) >= (pair ? 3 : 4);
+    planes += g.mpl[q];
+    anypair = anypair || pair;
+    xpair = xpair && xc && pair;
   }
-  g.mat = fits && !(wave && big);
+  // axes some of whose pencils have no wavefront kernel
+  int lack[3] = {0, 0, 0};
+  for (int q = 0; q < 3; ++q)
+    for (int pass = 0; pass < 5; ++pass)
+      if (!g.wE[q][pass]) lack[slot_axis(pass)] = 1;
+  const bool wave = !lack[0] && !lack[1] && !lack[2];
+  const int a = lack[0] ? 0 : (lack[1] ? 1 : 2);
+  bool thin = lack[0] + lack[1] + lack[2] == 1 && g.n[a] < 16;
+  thin = thin && (a == 0 ? xpair : anypair && g.rbytes == 8 && planes > 256);
+  for (int i = 1; i < 3; ++i)
+    if (i != a) thin = thin && (a == 0 ? g.n[i] < 32 || g.n[i] % 32 == 0 : g.n[i] >= 32);
+  g.mat = fits && !(big && (wave || thin));
 }
-
-// Pass slots: x fwd, y fwd, fused z, y inv, x inv, and for C0 plans z fwd and
-// z inv.
-constexpr int NPASS = 7;
-inline int slot_axis(int pass) { return pass == 0 || pass == 4 ? 0 : (pass == 1 || pass == 3 ? 1 : 2); }
 
 int make_geometry(const fm_plan_desc* d, Geometry& g) {
   if (!d) return fail(FM_E_INVALID_ARG, "null descriptor");

@@ -48,3 +48,32 @@ def test_wavefront_offsets(geometry):
         assert geometry((2000, 2048, 64), W.FP64, c0, green=W.GREEN_C0)[1][q][5:] == ["64x1", "64x1"]
     # (the component with the longest spectrum: cosines along x and y)
     assert ["-", "-"] in [k[5:] for k in geometry(n, W.FP64, c0, green=W.GREEN_C0)[1]]
+
+
+# one short axis (fewer than 16 cells) without a wavefront kernel: plans whose
+# planes of complex data are few, or fill a second round in FP64, stay on the
+# axis passes; their neighbours, and grids with a longer or a second such
+# axis, run on the matrix cores
+@pytest.mark.parametrize("n,pattern,fp32,fp64", [
+    ((6, 64, 64), "PPP", 0, 0), ((6, 64, 64), "PPD", 0, 0), ((6, 64, 64), "DPP", 1, 1), ((6, 64, 64), "DNN", 1, 1),
+    ((4, 64, 32), "PPM", 0, 0), ((5, 96, 96), "PPP", 0, 0), ((5, 64, 96), "PPP", 0, 0), ((15, 64, 32), "PPP", 0, 0),
+    ((17, 64, 32), "PPP", 1, 1), ((10, 64, 48), "PPP", 1, 1), ((11, 48, 64), "PPP", 1, 1), ((11, 16, 32), "PPP", 1, 1), ((11, 16, 64), "PPP", 0, 0),
+    ((6, 64, 57), "PPP", 1, 1), ((6, 32, 32), "PPP", 1, 1), ((64, 7, 64), "PPP", 1, 1), ((64, 64, 7), "PPP", 1, 1),
+    ((96, 64, 5), "DPP", 1, 0), ((96, 9, 32), "NPP", 1, 0), ((96, 64, 5), "PPP", 1, 1), ((96, 48, 10), "DPP", 1, 0), ((96, 16, 9), "DPP", 1, 1),
+    ((64, 64, 5), "DPP", 1, 1), ((96, 64, 17), "DPP", 1, 1), ((96, 5, 96), "DNN", 1, 1), ((96, 11, 13), "DPP", 1, 1)])
+def test_short_axes(geometry, n, pattern, fp32, fp64):
+    assert geometry(n, W.FP32_MIXED, pattern)[0] == bool(fp32)
+    assert geometry(n, W.FP64, pattern)[0] == bool(fp64)
+
+
+# the lines of cubes with wavefront kernels throughout, and the longest axis
+# of either precision on the matrix cores
+@pytest.mark.parametrize("n,prec,pattern,mat", [
+    ((64, 64, 64), W.FP64, "DNN", 1), ((96, 96, 96), W.FP64, "DNN", 0), ((96, 96, 96), W.FP32_MIXED, "MMM", 0),
+    ((95, 95, 95), W.FP64, "DNN", 1), ((48, 48, 48), W.FP64, "PPP", 1), ((64, 64, 64), W.FP32_MIXED, "PPP", 0),
+    ((191, 5, 6), W.FP32_MIXED, "NNN", 1), ((192, 5, 6), W.FP32_MIXED, "NNN", 0),
+    ((127, 5, 6), W.FP64, "NNN", 1), ((128, 5, 6), W.FP64, "NNN", 0),
+    ((6, 127, 5), W.FP32_MIXED, "PPP", 1), ((6, 128, 5), W.FP32_MIXED, "PPP", 0),
+    ((6, 95, 5), W.FP64, "PPP", 1), ((6, 96, 5), W.FP64, "PPP", 0)])
+def test_matrix_lengths(geometry, n, prec, pattern, mat):
+    assert geometry(n, prec, pattern)[0] == bool(mat)
