@@ -161,6 +161,7 @@ def batch_sample(B, W, count=512, tol=1e-6, log=None):
     choices = {}
     for pl in plans32:
         c = "".join(str(v) for v in pl.autotune(n_iter=3)["choice"])
+        c = "matrix" if pl.matrix_transforms() else c
         choices[c] = choices.get(c, 0) + 1
     tune_s = time.time() - t0
     log(f"batch: {count} problems generated in {gen_s:.1f} s, FP32 plans {setup32:.2f} s, autotuned in {tune_s:.1f} s")

@@ -256,8 +256,10 @@ int fm_residual(fm_plan* plan, const fm_load_step* step, const double* d_uf, dou
  * events on the plan's stream around each of the FM_N_KERNELS launches, and
  * writes the mean duration in milliseconds per kernel to ms[FM_N_KERNELS]
  * (order: stress+divergence, control, gram, alpha, x-forward, y-forward,
- * z-forward+Green+inverse, y-inverse, x-inverse+update).  Overwrites the
- * plan's displacement. */
+ * z-forward+Green+inverse, y-inverse, x-inverse+update).  A plan on the
+ * matrix-core transforms has no y passes of its own: their two entries are 0
+ * and the z entry holds the fused y-z kernel.  Overwrites the plan's
+ * displacement. */
 #define FM_N_KERNELS 9
 int fm_profile_iterations(fm_plan* plan, const fm_load_step* step, int32_t n_iter, double* ms);
 
@@ -283,13 +285,18 @@ int fm_set_graph_launch(int enable);
  * that fill (time divided by the repetitions): its cost when other solves
  * share the device, as in fm_batch_solve and the server.  A plan whose
  * spectral part runs on the matrix-core transforms (short and odd axes)
- * keeps them when they are faster than the five chosen passes together;
- * choice and ms describe the axis passes in either case.
+ * keeps them when they are faster than the five chosen passes together
+ * (fm_plan_matrix_transforms tells which it kept); choice and ms describe the
+ * axis passes in either case.
  * choice[5] (host, optional) receives the chosen candidate per pass;
  * ms[4*5] (host, optional) the mean time in ms per candidate and pass (-1 if
  * not applicable).  Overwrites the plan's displacement and spectral buffers
  * (reset it with fm_set_material before solving). */
 int fm_autotune(fm_plan* plan, const fm_load_step* step, int32_t n_iter, int32_t* choice, double* ms);
+
+/* 1 if the spectral part of the plan's iterations runs on the matrix-core
+ * transforms, 0 if on the axis passes (-1 for a null plan). */
+int fm_plan_matrix_transforms(const fm_plan* plan);
 
 /* Iterations performed by the last fm_solve / fm_batch_solve of this plan. */
 int64_t fm_plan_total_iterations(const fm_plan* plan);

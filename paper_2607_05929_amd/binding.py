@@ -90,6 +90,7 @@ EXPORTS = {
     "fm_profile_iterations": (C.c_int, [C.c_void_p, C.POINTER(LoadStep), C.c_int32,
                                         C.POINTER(C.c_double)]),
     "fm_plan_total_iterations": (C.c_int64, [C.c_void_p]),
+    "fm_plan_matrix_transforms": (C.c_int, [C.c_void_p]),
     "fm_plan_destroy": (None, [C.c_void_p]),
     "fm_server_create": (C.c_int, [C.c_void_p, C.c_size_t, C.c_int32, C.c_void_p,
                                    C.POINTER(C.c_void_p)]),
@@ -343,7 +344,9 @@ class Plan:
 
     def autotune(self, step=None, n_iter=4):
         """Pick the fastest transform kernel per axis pass (fm_autotune), then
-        reset the displacement.  Returns the choices and the timing table."""
+        reset the displacement.  Returns the choices and the timing table of
+        the axis passes (matrix_transforms tells whether the plan kept its
+        matrix-core transforms instead)."""
         step = self.prob.steps[0] if step is None else step
         choice = (C.c_int32 * 5)()
         ms = (C.c_double * 20)()
@@ -357,6 +360,10 @@ class Plan:
                                     len(self.prob.materials), self._tab), "fm_set_material")
         if sync:
             self.torch.cuda.current_stream().synchronize()
+
+    def matrix_transforms(self):
+        """True if the spectral part runs on the matrix-core transforms, False on the axis passes."""
+        return lib().fm_plan_matrix_transforms(self.handle) == 1
 
     def total_iterations(self):
         return int(lib().fm_plan_total_iterations(self.handle))
