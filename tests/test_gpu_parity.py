@@ -64,7 +64,9 @@ def test_green_apply(B, prec, seed, n, scheme, green):
 # doubled DTT lengths) take the kernels with two or four pencils per
 # wavefront (32 / 16 lanes each), also on the x passes with their wider tiles;
 # the 96-cell y and z axes reach the FP32 kind-specific kernels of 96- and
-# 192-point pencils on complex (post-r2c) data.
+# 192-point pencils on complex (post-r2c) data.  Grids without an axis past the
+# matrix cores' sizes (most from (48, 16, 5) on) run there instead:
+# test_gpu_axis_passes.py holds these pencils to the axis passes.
 WAVE_SHAPES = [(256, 6, 5), (6, 256, 5), (5, 6, 256), (96, 160, 6), (192, 7, 128), (64, 32, 384),
                (512, 5, 6), (6, 512, 5), (5, 6, 512),
                (48, 16, 5), (16, 48, 7), (5, 24, 48), (24, 7, 16), (8, 48, 24), (6, 96, 5), (5, 6, 96)]
