@@ -181,9 +181,20 @@ struct PassDesc {
   const double* gc2[3];           // cos^2(xi/2)
   int32_t scheme, green_lam;      // green_lam: 1 uses lambda0 (B0), 0 for 2mu0
   double h, lam0, mu0;
-  MatAxis mx[3];                  // matrix-core passes: the component's axes
+};
+
+// One component of one solve on the matrix-core transforms (device).
+struct MatDesc {
+  MatAxis x[3];
+  const void* D;                  // component base of the D ring (x forward)
+  void* delta;                    // component base of the delta ring (x inverse)
+  int64_t ring_stride;            // reals between slots of either
+  void* T;                        // spectral planes
+  double* uf;                     // component base of u^f
+  const Ctrl* ctrl;
+  double h, lam0, mu0;
+  int32_t q, scheme, green_lam;
   int32_t pair;                   // 1: some axis transforms complex data (its plane kernel pairs real and imaginary parts)
-  const Ctrl* ctrl;               // control block of the solve
 };
 
 }  // namespace fm

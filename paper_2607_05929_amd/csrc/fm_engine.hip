@@ -412,7 +412,7 @@ inline bool slot_used(const Geometry& g, int pass) {
   return true;
 }
 
-size_t group_bytes_for(int nsolves, int64_t tiles_total[NWL]);
+size_t group_bytes_for(int nsolves, int nmat, int64_t tiles_total[NWL]);
 
 // Stress-divergence tiling of a group member.  A lone solve keeps the
 // tiling of its geometry, which shortens the tiles until the grid fills the
@@ -473,10 +473,12 @@ void tiles_of(const Geometry& g, int64_t t[NWL]) {
   }
 }
 
-size_t group_bytes_for(int nsolves, int64_t tiles_total[NWL]) {
+// (nmat: solves on the matrix-core transforms)
+size_t group_bytes_for(int nsolves, int nmat, int64_t tiles_total[NWL]) {
   size_t b = 0;
   b += align_up(sizeof(SolveDev) * nsolves);
   b += align_up(sizeof(PassDesc) * nsolves * 3 * NPASS);
+  b += align_up(sizeof(MatDesc) * nmat * 3);
   for (int i = 0; i < NWL; ++i) b += align_up(sizeof(int2) * std::max<int64_t>(1, tiles_total[i]));
   b += align_up(sizeof(int) * nsolves);
   return b;
@@ -541,7 +543,11 @@ void make_layout(const fm_plan_desc* d, const Geometry& g, Layout& L) {
     for (int pass = 0; pass < NPASS; ++pass) gmax.cols[q][pass] = 1;
   int64_t t[NWL];
   tiles_of(gmax, t);
-  L.group_bytes = group_bytes_for(1, t);
+  L.group_bytes = group_bytes_for(1, 0, t);
+  if (g.mat) {
+    tiles_of(g, t);
+    L.group_bytes = std::max(L.group_bytes, group_bytes_for(1, 1, t));
+  }
   L.group = take(L.group_bytes);
   L.total = o + ALIGN;   // slack for base alignment
 }
@@ -699,6 +705,7 @@ struct fm_plan {
   char* ws = nullptr;
   SolveDev sd{};           // host image of the device descriptor
   PassDesc pd[3][NPASS]{};   // host images, per component and pass slot
+  MatDesc md[3]{};           // and per component on the matrix-core transforms
   bool material_set = false;
   int n_mat = 0;
   bool has_cp = false;     // some material is crystal plasticity
@@ -748,6 +755,7 @@ struct Group {
   hipStream_t stream = nullptr;
   SolveDev* S = nullptr;
   PassDesc* P = nullptr;
+  MatDesc* M = nullptr;   // three per solve on the matrix-core transforms
   int2* wl[NWL]{};     // voxel, node, stress-divergence: whole lists; passes: concatenated buckets
   int64_t nwl[NWL]{};
   int64_t boff[NPASS][NBUCKET]{};   // start of each bucket inside wl[WL_PASS0 + slot]
@@ -827,32 +835,6 @@ void fill_pass_descs(fm_plan* p) {
       for (int i = 0; i < d.nrad; ++i) d.rad[i] = rad[i];
       d.F = g.F[q][pass];
       d.tw = ws + p->lay.tw_off[q][axis];
-      d.ctrl = (const Ctrl*)(ws + p->lay.ctrl);
-      d.pair = g.mat && g.mns[q] == 2;
-      if (g.mat)
-        for (int a = 0; a < 3; ++a) {
-          MatAxis& m = d.mx[a];
-          const int kt = g.mkt[q][a], n = g.n[a], rem = n / 2 + 1 - 16 * (kt - 1);
-          const MatBlock b = mat_block(kt, n, g.rbytes);
-          char* t = ws + p->lay.mat_off[q][a];
-          m.kind = g.kinds[q][a];
-          m.n = n;
-          m.cls = g.mcls[q][a];
-          m.kt = kt;
-          // a step covers four columns: one per lane group in the natural
-          // order (z forward, FP64 results), four apart in the quad order
-          // (all four unless one holds every column)
-          const int natural = rem <= 4 ? 1 : 4, quad = rem <= 1 ? 1 : 4;
-          m.rlf = a == 2 ? natural : quad;
-          m.rli = g.rbytes == 8 ? natural : quad;
-          mat_slots(m.kind, m.cls, n, m.cU, m.cV);
-          int cnt;
-          raw_range(m.kind, n, m.j0, cnt);
-          m.j1 = m.j0 + cnt;
-          m.fU = t; m.fV = t + b.half; m.iU = t + 2 * b.half; m.iV = t + 3 * b.half;
-          m.gs = (const double*)(t + b.gs);
-          m.gz = t + b.gz;
-        }
       switch (pass) {
         case 0:   // x forward: D ring rows -> A (M0 per row)
           d.cplx_in = 0; d.cplx_out = c1; d.packed = 1;
@@ -936,17 +918,44 @@ void fill_pass_descs(fm_plan* p) {
           d.in = Cz; d.out = B;
           break;
       }
-      if (g.mat) {
-        if (pass == 0 || pass == 4) {
-          d.cols = 16 * MAT_WAVES;
-          d.tiles_p0 = (int)cdiv(d.n_p0, d.cols);
-        } else if (pass == 2) {
-          d.in = d.out = A;
-          d.tiles_p0 = g.mpl[q];
-          d.n_p1 = 1;
-        }
-      }
     }
+    if (!g.mat) continue;
+    MatDesc& m = p->md[q];
+    std::memset(&m, 0, sizeof(m));
+    for (int a = 0; a < 3; ++a) {
+      MatAxis& x = m.x[a];
+      const int kt = g.mkt[q][a], n = g.n[a], rem = n / 2 + 1 - 16 * (kt - 1);
+      const MatBlock b = mat_block(kt, n, g.rbytes);
+      char* t = ws + p->lay.mat_off[q][a];
+      x.kind = g.kinds[q][a];
+      x.n = n;
+      x.cls = g.mcls[q][a];
+      x.kt = kt;
+      // a step covers four columns: one per lane group in the natural
+      // order (z forward, FP64 results), four apart in the quad order
+      // (all four unless one holds every column)
+      const int natural = rem <= 4 ? 1 : 4, quad = rem <= 1 ? 1 : 4;
+      x.rlf = a == 2 ? natural : quad;
+      x.rli = g.rbytes == 8 ? natural : quad;
+      mat_slots(x.kind, x.cls, n, x.cU, x.cV);
+      int cnt;
+      raw_range(x.kind, n, x.j0, cnt);
+      x.j1 = x.j0 + cnt;
+      x.fU = t; x.fV = t + b.half; x.iU = t + 2 * b.half; x.iV = t + 3 * b.half;
+      x.gs = (const double*)(t + b.gs);
+      x.gz = t + b.gz;
+    }
+    m.D = ws + p->lay.Dring + R * (size_t)q * g.Nn;
+    m.delta = ws + p->lay.dring + R * (size_t)q * g.Nn;
+    m.ring_stride = 3 * g.Nn;
+    m.T = A;
+    m.uf = (double*)(ws + p->lay.uf) + (size_t)q * g.Nn;
+    m.ctrl = (const Ctrl*)(ws + p->lay.ctrl);
+    m.h = p->d.h; m.lam0 = p->d.lambda0; m.mu0 = p->d.mu0;
+    m.q = q;
+    m.scheme = p->d.scheme;
+    m.green_lam = p->d.green == FM_GREEN_B0;
+    m.pair = g.mns[q] == 2;
   }
 }
 
@@ -1102,15 +1111,19 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
     tiles_of(plans[i]->g, ti);
     for (int k = 0; k < NWL; ++k) t[k] += ti[k];
   }
-  const size_t need = group_bytes_for(ns, t);
+  int nmat = 0;
+  for (int i = 0; i < ns; ++i) nmat += plans[i]->g.mat;
+  const size_t need = group_bytes_for(ns, nmat, t);
   if (need > bytes) return fail(FM_E_WORKSPACE, "group workspace too small");
   size_t o = 0;
   G.S = (SolveDev*)(dev + o); o += align_up(sizeof(SolveDev) * ns);
   G.P = (PassDesc*)(dev + o); o += align_up(sizeof(PassDesc) * ns * 3 * NPASS);
+  G.M = (MatDesc*)(dev + o); o += align_up(sizeof(MatDesc) * nmat * 3);
   for (int k = 0; k < NWL; ++k) { G.wl[k] = (int2*)(dev + o); o += align_up(sizeof(int2) * std::max<int64_t>(1, t[k])); }
   G.ids = (int*)(dev + o);
   std::vector<SolveDev> S(ns);
   std::vector<PassDesc> P((size_t)ns * 3 * NPASS);
+  std::vector<MatDesc> M;
   std::vector<int2> wl[4];          // voxel, node, stress-divergence, C0 apply tiles
   std::vector<int2> pb[NPASS][NBUCKET];
   std::vector<int> ids(ns);
@@ -1139,11 +1152,13 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
         P[di] = d;
         if (!slot_used(p->g, pass)) continue;
         if (p->g.mat) {
-          if (pass == 1 || pass == 3) continue;
           const Geometry& mg = p->g;
+          if (pass == 0) M.push_back(p->md[q]);
+          if (pass == 1 || pass == 3) continue;
           const int b = pass == 2 ? mat_bucket(B_MATP, mg.mns[q], std::max(mg.mkt[q][1], mg.mkt[q][2]))
                                   : mat_bucket(B_MATX, 1, mg.mkt[q][0]);
-          for (int ty = 0; ty < d.tiles_p0; ++ty) pb[pass][b].push_back(make_int2(di, ty));
+          const int nt = pass == 2 ? mg.mpl[q] : (int)cdiv(mg.N[1] * mg.N[2], 16 * MAT_WAVES);
+          for (int ty = 0; ty < nt; ++ty) pb[pass][b].push_back(make_int2((int)M.size() - 1, ty));
           if (pass == 2) G.blds[pass][b] = std::max(G.blds[pass][b], mg.mlds[q]);
           continue;
         }
@@ -1195,6 +1210,7 @@ int build_group(Group& G, fm_plan* const* plans, int ns, char* dev, size_t bytes
   }
   HIPCHK(hipMemcpyAsync(G.S, S.data(), sizeof(SolveDev) * ns, hipMemcpyHostToDevice, stream));
   HIPCHK(hipMemcpyAsync(G.P, P.data(), sizeof(PassDesc) * P.size(), hipMemcpyHostToDevice, stream));
+  if (!M.empty()) HIPCHK(hipMemcpyAsync(G.M, M.data(), sizeof(MatDesc) * M.size(), hipMemcpyHostToDevice, stream));
   for (int k = 0; k < NWL; ++k) {
     const std::vector<int2>& v = k == WL_VOX ? wl[0] : k == WL_NODE ? wl[1] : k == WL_SDIV ? wl[2]
                                  : k == WL_C0 ? wl[3] : pl[k - WL_PASS0];
@@ -1477,8 +1493,8 @@ int launch_bucket(const Group& G, int pk, int b) {
   if (b >= B_MATX) {
     const int k = b >= B_MATP ? b - B_MATP : b - B_MATX;
     const bool ok = b >= B_MATP
-                        ? mat_launch_plane(sizeof(R), k % 6 + 1, k / 6 + 1, grid.x, lds, st, G.P, wl)
-                        : mat_launch_x(sizeof(R), pk == 4, k % 6 + 1, grid.x, st, G.P, wl);
+                        ? mat_launch_plane(sizeof(R), k % 6 + 1, k / 6 + 1, grid.x, lds, st, G.M, wl)
+                        : mat_launch_x(sizeof(R), pk == 4, k % 6 + 1, grid.x, st, G.M, wl);
     if (!ok) return fail(FM_E_INVALID_ARG, "internal: no matrix-core kernel of this size");
   } else if (b >= 24) {
     const int set = (b - 24) / 10, kind = ((b - 24) % 10) >> 1, packed = b & 1;

@@ -64,8 +64,8 @@ hipError_t mat_set_limits(int rbytes);
 void mat_build_tables(int rbytes, const MatTableArgs& a, hipStream_t st);
 // x passes (inverse = 0 / 1) and the fused y-z plane pass; kt: tiles of the
 // longest axis involved, ns: pencil sets per wavefront of a plane block.
-bool mat_launch_x(int rbytes, int inverse, int kt, unsigned grid, hipStream_t st, const PassDesc* P, const int2* wl);
-bool mat_launch_plane(int rbytes, int kt, int ns, unsigned grid, size_t lds, hipStream_t st, const PassDesc* P,
+bool mat_launch_x(int rbytes, int inverse, int kt, unsigned grid, hipStream_t st, const MatDesc* M, const int2* wl);
+bool mat_launch_plane(int rbytes, int kt, int ns, unsigned grid, size_t lds, hipStream_t st, const MatDesc* M,
                       const int2* wl);
 
 }  // namespace fm

@@ -222,22 +222,22 @@ __device__ __forceinline__ int plane_V(const MatAxis& x, int a) { return x.kind 
 // x forward.  One wavefront per 16 rows, rows read as quads, spectral planes
 // written with the 16 rows contiguous.
 template <typename R, int KT>
-__global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xf(const PassDesc* __restrict__ descs,
+__global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xf(const MatDesc* __restrict__ descs,
                                                            const int2* __restrict__ work) {
   const int2 wk = work[blockIdx.x];
-  const PassDesc& d = descs[wk.x];
+  const MatDesc& d = descs[wk.x];
   const FM_GLOBAL Ctrl* C = gconst(d.ctrl);
-  const MatAxis x = d.mx[0];
+  const MatAxis x = d.x[0];
   const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
-  const int64_t NR = d.n_p0;
+  const int64_t NR = (int64_t)(d.x[1].n + 1) * (d.x[2].n + 1);
   const int64_t r0 = ((int64_t)wk.y * MAT_WAVES + (threadIdx.x >> 6)) * 16;
   if (r0 >= NR || C->status != ST_RUNNING) return;
   Frag<R, KT> f;
   f.load(x.fU, x.fV, 0, KT, lane);
   V4<R> e[1][KT], o[1][KT];
   {
-    const int64_t row = min(r0 + p, NR - 1) * d.in_s1;
-    const FM_GLOBAL R* ring = gconst((const R*)d.ring);
+    const int64_t row = min(r0 + p, NR - 1) * (x.n + 1);
+    const FM_GLOBAL R* ring = gconst((const R*)d.D);
     const int64_t stride = d.ring_stride;
     const int nd = C->n_d;
     RowRaw<R, KT> raw;
@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xf(const PassDesc* __res
     }
     raw.operands(x, KT, g, e[0], o[0]);
   }
-  FM_GLOBAL R* T = gmut((R*)d.out) + r0 + p;
+  FM_GLOBAL R* T = gmut((R*)d.T) + r0 + p;
   const bool okr = r0 + p < NR;
   for (int mt = 0; mt < KT; ++mt) {
     V4<R> u[1], v[1];
@@ -288,21 +288,21 @@ __global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xf(const PassDesc* __res
 // x inverse and displacement update u^f += w - sum_k beta_k delta_k; the new
 // increment goes into the ring (FP64 accumulator).
 template <typename R, int KT>
-__global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xi(const PassDesc* __restrict__ descs,
+__global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xi(const MatDesc* __restrict__ descs,
                                                            const int2* __restrict__ work) {
   const int2 wk = work[blockIdx.x];
-  const PassDesc& d = descs[wk.x];
+  const MatDesc& d = descs[wk.x];
   const FM_GLOBAL Ctrl* C = gconst(d.ctrl);
-  const MatAxis x = d.mx[0];
+  const MatAxis x = d.x[0];
   const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
-  const int64_t NR = d.n_p0;
+  const int64_t NR = (int64_t)(d.x[1].n + 1) * (d.x[2].n + 1);
   const int64_t r0 = ((int64_t)wk.y * MAT_WAVES + (threadIdx.x >> 6)) * 16;
   if (r0 >= NR) return;
   Frag<R, KT> f;
   f.load(x.iU, x.iV, 0, KT, lane);
   V4<R> e[1][KT], o[1][KT];
   {
-    const FM_GLOBAL R* T = gconst((const R*)d.in) + min(r0 + p, NR - 1);
+    const FM_GLOBAL R* T = gconst((const R*)d.T) + min(r0 + p, NR - 1);
 #pragma unroll
     for (int t = 0; t < KT; ++t)
 #pragma unroll
@@ -325,9 +325,9 @@ __global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xi(const PassDesc* __res
   }
   if (C->status != ST_RUNNING) return;
   const int nb = C->n_b;
-  const FM_GLOBAL R* ring = gconst((const R*)d.ring);
+  const FM_GLOBAL R* ring = gconst((const R*)d.delta);
   const int64_t stride = d.ring_stride;
-  FM_GLOBAL R* dw = gmut((R*)d.ring) + (int64_t)C->slot_w * stride;
+  FM_GLOBAL R* dw = gmut((R*)d.delta) + (int64_t)C->slot_w * stride;
   FM_GLOBAL double* uf = gmut(d.uf);
   auto upd1 = [&](int64_t i, R w) {
     for (int q = 0; q < nb; ++q) w -= (R)C->beta[q] * ring[C->slot_b[q] * stride + i];
@@ -356,7 +356,7 @@ __global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xi(const PassDesc* __res
   };
   const int n = x.n, h = n >> 1;
   const bool okr = r0 + p < NR;
-  const int64_t row = (r0 + p) * d.out_s1;
+  const int64_t row = (r0 + p) * (x.n + 1);
   for (int mt = 0; mt < KT; ++mt) {
     V4<R> u[1], v[1];
     Frag<R, KT> fn;
@@ -405,7 +405,7 @@ __global__ void __launch_bounds__(64 * MAT_WAVES) k_mat_xi(const PassDesc* __res
 //
 // Per-column Green data: den(kz) = A cos^2(xi_z/2) + B sin^2(xi_z/2).
 template <typename R>
-__device__ __forceinline__ void green_ab(const PassDesc& d, double s0, double c0, double s1, double c1, R& A, R& B) {
+__device__ __forceinline__ void green_ab(const MatDesc& d, double s0, double c0, double s1, double c1, R& A, R& B) {
   double a[3], b[3];
   if (d.scheme == 0) {
     a[0] = s0 * c1; a[1] = c0 * s1; a[2] = 0;
@@ -443,13 +443,13 @@ __device__ __forceinline__ R green_f(R A, R B, const R* sc) {
 // coefficients of each row; the z slot frequencies.
 template <typename R, int KT, int NS>
 __global__ void __launch_bounds__(mat_plane_threads(sizeof(R), KT, NS), mat_plane_waves(sizeof(R), KT, NS)) k_mat_plane(
-    const PassDesc* __restrict__ descs, const int2* __restrict__ work) {
+    const MatDesc* __restrict__ descs, const int2* __restrict__ work) {
   extern __shared__ __align__(16) char smem[];
   R* sm = (R*)smem;
   const int2 wk = work[blockIdx.x];
-  const PassDesc& d = descs[wk.x];
+  const MatDesc& d = descs[wk.x];
   const FM_GLOBAL Ctrl* C = gconst(d.ctrl);
-  const MatAxis X = d.mx[0], Y = d.mx[1], Z = d.mx[2];
+  const MatAxis X = d.x[0], Y = d.x[1], Z = d.x[2];
   const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
   const int wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
   const int N1 = Y.n + 1, N2 = Z.n + 1, n1 = Y.n, n2 = Z.n;
@@ -466,7 +466,7 @@ __global__ void __launch_bounds__(mat_plane_threads(sizeof(R), KT, NS), mat_plan
   // matrix steps of tile KT - 1 (past the tiles of the shorter axis: zeros)
   const int yf = Y.kt == KT ? Y.rlf : 1, yi = Y.kt == KT ? Y.rli : 1;
   const int zf = Z.kt == KT ? Z.rlf : 1, zi = Z.kt == KT ? Z.rli : 1;
-  FM_GLOBAL R* T = gmut((R*)d.out) + (int64_t)plane0 * NR;
+  FM_GLOBAL R* T = gmut((R*)d.T) + (int64_t)plane0 * NR;
   const int ntz = (N2 + 15) >> 4;
   const int nt1 = (NS == 1 || px) ? ntz : (ntz + 1) >> 1;
   // rows of this wavefront's first tile; z[s]: z position of set s of a tile
@@ -855,13 +855,13 @@ __global__ void __launch_bounds__(256) k_mat_tables(MatTableArgs A) {
 }
 
 template <typename R, int INV>
-bool launch_x_kt(int kt, unsigned grid, hipStream_t st, const PassDesc* P, const int2* wl) {
+bool launch_x_kt(int kt, unsigned grid, hipStream_t st, const MatDesc* M, const int2* wl) {
   const dim3 G(grid), T(64 * MAT_WAVES);
 #define FM_MAT_X(K)                                                                                      \
   case K:                                                                                                \
     if constexpr (K <= mat_max_kt(sizeof(R), 1)) {                                                       \
-      if (INV) hipLaunchKernelGGL((k_mat_xi<R, K>), G, T, 0, st, P, wl);                                 \
-      else hipLaunchKernelGGL((k_mat_xf<R, K>), G, T, 0, st, P, wl);                                     \
+      if (INV) hipLaunchKernelGGL((k_mat_xi<R, K>), G, T, 0, st, M, wl);                                 \
+      else hipLaunchKernelGGL((k_mat_xf<R, K>), G, T, 0, st, M, wl);                                     \
       return true;                                                                                       \
     }                                                                                                    \
     return false;
@@ -873,12 +873,12 @@ bool launch_x_kt(int kt, unsigned grid, hipStream_t st, const PassDesc* P, const
 }
 
 template <typename R, int NS>
-bool launch_plane_kt(int kt, unsigned grid, size_t lds, hipStream_t st, const PassDesc* P, const int2* wl) {
+bool launch_plane_kt(int kt, unsigned grid, size_t lds, hipStream_t st, const MatDesc* M, const int2* wl) {
   const dim3 G(grid), T(mat_plane_threads(sizeof(R), kt, NS));
 #define FM_MAT_P(K)                                                                                      \
   case K:                                                                                                \
     if constexpr (K <= mat_max_kt(sizeof(R), NS)) {                                                      \
-      hipLaunchKernelGGL((k_mat_plane<R, K, NS>), G, T, lds, st, P, wl);                                 \
+      hipLaunchKernelGGL((k_mat_plane<R, K, NS>), G, T, lds, st, M, wl);                                 \
       return true;                                                                                       \
     }                                                                                                    \
     return false;
@@ -917,16 +917,16 @@ void mat_build_tables(int rbytes, const MatTableArgs& a, hipStream_t st) {
   else hipLaunchKernelGGL(k_mat_tables<double>, G, T, 0, st, a);
 }
 
-bool mat_launch_x(int rbytes, int inverse, int kt, unsigned grid, hipStream_t st, const PassDesc* P, const int2* wl) {
-  if (rbytes == 4) return inverse ? launch_x_kt<float, 1>(kt, grid, st, P, wl) : launch_x_kt<float, 0>(kt, grid, st, P, wl);
-  return inverse ? launch_x_kt<double, 1>(kt, grid, st, P, wl) : launch_x_kt<double, 0>(kt, grid, st, P, wl);
+bool mat_launch_x(int rbytes, int inverse, int kt, unsigned grid, hipStream_t st, const MatDesc* M, const int2* wl) {
+  if (rbytes == 4) return inverse ? launch_x_kt<float, 1>(kt, grid, st, M, wl) : launch_x_kt<float, 0>(kt, grid, st, M, wl);
+  return inverse ? launch_x_kt<double, 1>(kt, grid, st, M, wl) : launch_x_kt<double, 0>(kt, grid, st, M, wl);
 }
 
-bool mat_launch_plane(int rbytes, int kt, int ns, unsigned grid, size_t lds, hipStream_t st, const PassDesc* P,
+bool mat_launch_plane(int rbytes, int kt, int ns, unsigned grid, size_t lds, hipStream_t st, const MatDesc* M,
                       const int2* wl) {
   if (rbytes == 4)
-    return ns == 2 ? launch_plane_kt<float, 2>(kt, grid, lds, st, P, wl) : launch_plane_kt<float, 1>(kt, grid, lds, st, P, wl);
-  return ns == 2 ? launch_plane_kt<double, 2>(kt, grid, lds, st, P, wl) : launch_plane_kt<double, 1>(kt, grid, lds, st, P, wl);
+    return ns == 2 ? launch_plane_kt<float, 2>(kt, grid, lds, st, M, wl) : launch_plane_kt<float, 1>(kt, grid, lds, st, M, wl);
+  return ns == 2 ? launch_plane_kt<double, 2>(kt, grid, lds, st, M, wl) : launch_plane_kt<double, 1>(kt, grid, lds, st, M, wl);
 }
 
 }  // namespace fm

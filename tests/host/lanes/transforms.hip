@@ -109,28 +109,26 @@ int run(fm_plan* p, int terms, unsigned seed, std::vector<double>& x, std::vecto
       }
     }
     std::map<const void*, char*> tab;
-    for (int pass = 0; pass < 5; ++pass) {
-      PassDesc& d = G.P[q * NPASS + pass];
-      d.ctrl = cg;
-      if (pass == 0) { d.ring = ring; d.out = T[q]; }
-      if (pass == 2) d.in = d.out = T[q];
-      if (pass == 4) { d.in = T[q]; d.ring = delta[q]; d.uf = uf[q]; }
-      d.ring_stride = step / sizeof(R);
-      for (int a = 0; a < 3; ++a) {
-        MatAxis& m = d.mx[a];
-        auto move = [&](const void*& t, size_t bytes) {
-          char*& to = tab[t];
-          size_t s;
-          if (!to) { to = guarded(bytes, 1, s); std::memcpy(to, t, bytes); }
-          t = to;
-        };
-        const size_t half = (size_t)m.kt * m.kt * 256 * sizeof(R);
-        move(m.fU, half); move(m.fV, half); move(m.iU, half); move(m.iV, half);
-        const void* gs = m.gs;
-        move(gs, (size_t)64 * m.kt * 8);
-        m.gs = (const double*)gs;
-        move(m.gz, (size_t)64 * m.kt * sizeof(R));
-      }
+    MatDesc& d = G.M[q];
+    d.ctrl = cg;
+    d.D = ring;
+    d.delta = delta[q];
+    d.ring_stride = step / sizeof(R);
+    d.T = T[q];
+    d.uf = uf[q];
+    for (MatAxis& m : d.x) {
+      auto move = [&](const void*& t, size_t bytes) {
+        char*& to = tab[t];
+        size_t s;
+        if (!to) { to = guarded(bytes, 1, s); std::memcpy(to, t, bytes); }
+        t = to;
+      };
+      const size_t half = (size_t)m.kt * m.kt * 256 * sizeof(R);
+      move(m.fU, half); move(m.fV, half); move(m.iU, half); move(m.iV, half);
+      const void* gs = m.gs;
+      move(gs, (size_t)64 * m.kt * 8);
+      m.gs = (const double*)gs;
+      move(m.gz, (size_t)64 * m.kt * sizeof(R));
     }
   }
   for (int slot : {0, 1, 2, 3, 4})
