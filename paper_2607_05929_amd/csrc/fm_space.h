@@ -332,14 +332,14 @@ __global__ void __launch_bounds__(64, 2) k_stress(const SolveDev* __restrict__ S
 // Fused stress + divergence of one iteration.
 //
 // A block owns a tile of SD_TX x SD_TY node columns and sd_zc node layers
-// (at most SD_ZC; fewer on small grids and for the costly plastic laws, so
-// that there are enough blocks to fill the GPU).
+// (at most SD_ZC; fewer on small grids, so that there are enough blocks to
+// fill the GPU).
 // It marches up the layers: for voxel layer z it evaluates the behaviour law
 // on the 32 x 8 voxels that touch the tile (one per thread, the tile plus a
 // one-voxel halo; crystal plasticity reads them from its stress pass
 // instead), sums each voxel column's contributions of layers z-1 and z into
-// LDS partials, then forms the divergence at node layer z.  The stress of an
-// elastic solve never goes to memory.  Outside the grid a halo voxel holds the periodic image
+// LDS partials, then forms the divergence at node layer z.  Only the stress of
+// crystal plasticity goes to memory.  Outside the grid a halo voxel holds the periodic image
 // along axes periodic for some component, and zero otherwise (see
 // node_div for the reflecting faces).  Every voxel's stress enters the
 // block partials (sum w |sigma|^2, sum sigma) exactly once, in the tile that
@@ -604,8 +604,8 @@ __device__ __forceinline__ void state_law_stress(const SolveDev& s, const double
 // the stresses, fixed at compile time so that every load of a layer is
 // unconditional and a wait for one leaves the later ones in flight.
 //   SD_ELASTIC  elastic laws (CT = double; sdiv_tile_f32 otherwise)
-//   SD_HEX1, SD_TETRA2  a solve with internal variables: strain and law in
-//       FP64 (law_eval_e64).  Evaluating them here instead of in a stress
+//   SD_HEX1, SD_TETRA2  a solve with internal variables but no crystal
+//       plasticity: strain and law in FP64 (state_law_stress).  Evaluating them here instead of in a stress
 //       pass saves writing and reading the stresses, and the crystal
 //       plasticity code its registers (192^3 HEX1 in FP32: 245 us, the stress
 //       pass and its reader 447 + 162 us; 80^3: 28 against 69 us).
