@@ -348,6 +348,10 @@ def main():
     aa_frac = 1.0 / prob.aa_period
     nbytes = kernel_bytes(prob, geom, 4, n_d=1 + aa_frac * (prob.aa_depth - 1),
                           n_b=aa_frac * (prob.aa_depth - 1), n_gram=prob.aa_depth)
+    if p32.matrix_transforms():
+        # one fused y-z pass over the planes of the x transform, no y passes
+        nbytes["z_green"] = 2 * sum(geom["s1"]) * 4
+        del nbytes["y_fwd"], nbytes["y_inv"]
     dom = max((k for k in prof if k in nbytes), key=lambda k: prof[k])
     iter_ms = sum(prof.values())
     iter_bytes = sum(nbytes.values())
@@ -355,7 +359,7 @@ def main():
                   "GBs": nbytes[k] / (prof[k] * 1e-3) / 1e9,
                   "frac_of_8TBs": nbytes[k] / (prof[k] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                   "frac_of_copy": nbytes[k] / (prof[k] * 1e-3) / 1e9 / copy_gbs}
-              for k in ("x_fwd", "y_fwd", "z_green", "y_inv", "x_inv_update")}
+              for k in ("x_fwd", "y_fwd", "z_green", "y_inv", "x_inv_update") if k in nbytes}
     tp_ms = sum(v["ms"] for v in passes.values())
     tp_bytes = sum(v["algorithmic_bytes"] for v in passes.values())
     if dom == "stress_div":
